@@ -5,9 +5,11 @@
 
 #include <algorithm>
 #include <chrono>
+#include <cmath>
 #include <condition_variable>
 #include <cstring>
 #include <deque>
+#include <limits>
 #include <mutex>
 #include <new>
 #include <string>
@@ -178,6 +180,15 @@ hipError_t mark_use(const mstar_plan* plan, hipStream_t s) {
     e = hipEventRecord(plan->blk->last_use, s);
     if (e == hipSuccess) plan->blk->last_use_set = true;
     return e;
+}
+
+// sm_scale * log2(e) as hi + lo, both positive: hi rounded down, lo the rest
+// (at least a tiny part of hi, so that lo * -inf stays -inf).
+void split_scale(float sm_scale, float& hi, float& lo) {
+    const double c = (double)sm_scale * 1.4426950408889634;
+    hi = (float)c;
+    if ((double)hi > c) hi = std::nextafterf(hi, 0.0f);
+    lo = std::max((float)(c - (double)hi), std::max(hi * 0x1p-60f, std::numeric_limits<float>::denorm_min()));
 }
 
 bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
@@ -385,6 +396,7 @@ MSTAR_EXPORT int mstar_attn_fwd_timed(const mstar_plan_t* plan, const void* q, c
     a.num_pages = h.params.num_pages;
     a.sm_scale = h.params.sm_scale;
     a.scale_log2 = h.params.sm_scale * 1.4426950408889634f;
+    split_scale(h.params.sm_scale, a.scale_hi, a.scale_lo);
     hipStream_t s = stream;
 
     hipError_t e;

@@ -28,6 +28,7 @@ struct KArgs {
     int32_t hq, hkv, group, bt_stride, num_pages;
     float sm_scale;
     float scale_log2;  // sm_scale * log2(e)
+    float scale_hi, scale_lo;  // the same as a sum of two positive parts (fp32 kernel)
 };
 
 struct MArgs {

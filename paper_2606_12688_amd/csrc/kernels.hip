@@ -46,6 +46,10 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+__device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Workgroup and work-item indices straight from the hardware.  The runtime
@@ -1085,100 +1089,285 @@ __global__ __launch_bounds__(256, RB == 4 ? 1 : 2) void few_kernel(KArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// fp32 kernel: one wave per (query row, head); lanes take 64 keys at a time
-// for the scores and the head dimension for the weighted value sum.  All
-// arithmetic in fp32 with the accurate exp/log.
+// fp32 kernel: one workgroup = up to 16 (query row, head) rows of one KV head
+// against every key they see; its waves take interleaved 16-key steps (one
+// page each) and their results are combined through LDS.
+//
+// Both products run on 16x16x4 fp32 MFMAs, which multiply and accumulate in
+// full fp32: lane l (group G = l / 16, n = l % 16) supplies A[n][G] and
+// B[G][n] and receives D[4G .. 4G+3][n].  The order of a contraction is free,
+// so both operands of a step come from 16-byte loads: scores S^T = K Q^T take
+// dims 16 j + 4 G + c in step (j, c) (lane n reads its key's 16 bytes at dim
+// 16 j + 4 G); values O^T = V^T P^T take key 4 G + c in step c, whose
+// probability the lane already holds, and output row m of block (h, e) stands
+// for dim 64 h + 4 m + e (lane n reads key 4 G + c's 16 bytes at dim 64 h +
+// 4 n).  K and V go straight into registers; nothing passes through LDS but
+// the combine.
+//
+// Bound: the fp32 matrix rate (64 MFMAs of 32 cycles per 16 rows x 16 keys at
+// D = 128) once a few hundred items are in flight, latency below that.  One
+// wave per (row, head) with scalar dot products, each reading all of its keys
+// by itself, took 350 us where this takes 40 us (four prompts of 246-782
+// tokens and four decode rows, 8/2 heads, D = 128: 2.3 GFLOP); four prompts of
+// 5-64 tokens at D = 64: 8.1 -> 5.5 us.  Four waves per workgroup: eight have
+// the longest item done sooner, but only one such workgroup fits a CU at D =
+// 128, which bares every item's first loads and its combine (55 us).
 // ---------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(256) void f32_kernel(KArgs a) {
-    constexpr int E = D / 64;
-    __shared__ float q_lds[4][D];
+template <int D, int NW>
+__global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 3) void f32_kernel(KArgs a) {
+    constexpr int KJ = D / 16;  // 16-byte K (and Q) pieces per lane
+    constexpr int VH = D / 64;  // 16-byte V pieces per lane and key
+    __shared__ __attribute__((aligned(16))) float o_lds[NW][16 * D];
+    __shared__ float ml_lds[2][NW][16];
+
     const WorkItem it = a.items[wg_id()];
     const SeqInfo si = a.seqs[it.seq];
-    const int wave = thread_id() >> 6, lane = thread_id() & 63;
-    const int r = wave;
-    if (r >= it.nrows) return;
-    const int i = it.row0 + r;
-    int32_t lo, hi;
-    row_interval(a, si, it, i, lo, hi);
-    const int kvh = it.head / a.group;
+    // The item stands for query rows row0 .. row0 + nrows - 1 of one head; the
+    // G items of a KV head's group share their (row, head) pairs out as slices
+    // of 16, so that one read of K and V serves rows of several heads.  Items
+    // past the last slice have nothing to do.
+    const int G = a.group;
+    const int kvh = it.head / G;
+    const int p0 = (it.head - kvh * G) * 16;
+    const int np = min(it.nrows * G - p0, 16);
+    if (np <= 0) return;
+    const int wave = __builtin_amdgcn_readfirstlane(thread_id() >> 6) & (NW - 1), lane = thread_id() & 63;
+    const int n = lane & 15, grp = lane >> 4;
     const int32_t* bt_row = a.bt + (int64_t)it.seq * a.bt_stride;
-    const float* qg = reinterpret_cast<const float*>(a.q) + ((int64_t)(si.q_start + i) * a.hq + it.head) * D;
-    const float* kg = reinterpret_cast<const float*>(a.k);
-    const float* vg = reinterpret_cast<const float*>(a.v);
-#pragma unroll
-    for (int e = 0; e < E; ++e) q_lds[wave][lane + 64 * e] = qg[lane + 64 * e];
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_wave_barrier();
+    const RowGroup rg;
 
-    float m = kNegInf, l = 0.0f, acc[E];
+    // ---- this lane's row; the slice's bounds (intervals never shrink) ---------
+    const bool valid = n < np;
+    const int pr = p0 + (valid ? n : 0);
+    const int qi = it.row0 + pr / G, head = kvh * G + pr % G;
+    int32_t lo, hi, lo_min, lo_max, hi_min, hi_max;
+    row_interval(a, si, it, qi, lo, hi);
+    if (!valid) lo = hi = 0;
+    row_interval(a, si, it, it.row0 + p0 / G, lo_min, hi_min);
+    row_interval(a, si, it, it.row0 + (p0 + np - 1) / G, lo_max, hi_max);
+    float4 qf[KJ];
+    {
+        const float* q = reinterpret_cast<const float*>(a.q) + ((int64_t)(si.q_start + qi) * a.hq + head) * D;
 #pragma unroll
-    for (int e = 0; e < E; ++e) acc[e] = 0.0f;
-    for (int32_t kb = lo; kb < hi; kb += 64) {
-        const int32_t t = kb + lane;
-        float s = kNegInf;
-        // this lane's key: its V row (page 0 for a bad page, whose key reads as zeros)
-        int32_t vrow = 0;
-        bool vok = false;
-        if (t < hi) {
-            const int32_t page = bt_row[t >> 4];
-            vok = (uint32_t)page < (uint32_t)a.num_pages;
-            vrow = vok ? (page * 16 + (t & 15)) : 0;
-            if (vok) {
-                const float* kr = kg + (((int64_t)page * 16 + (t & 15)) * a.hkv + kvh) * D;
-                float dot = 0.0f;
-                for (int d = 0; d < D; d += 4) {
-                    const float4 kv = *reinterpret_cast<const float4*>(kr + d);
-                    dot = fmaf(q_lds[wave][d], kv.x, dot);
-                    dot = fmaf(q_lds[wave][d + 1], kv.y, dot);
-                    dot = fmaf(q_lds[wave][d + 2], kv.z, dot);
-                    dot = fmaf(q_lds[wave][d + 3], kv.w, dot);
-                }
-                s = dot * a.sm_scale;
-            } else {
-                atomicOr(a.err, 1);
-                s = 0.0f;  // the key reads as zeros
-            }
-        }
-        float cm = s;
-        for (int off = 32; off > 0; off >>= 1) cm = fmaxf(cm, __shfl_xor(cm, off, 64));
-        const float m_new = fmaxf(m, cm);
-        const float alpha = m == kNegInf ? 0.0f : expf(m - m_new);
-        const float p = t < hi ? expf(s - m_new) : 0.0f;
-        float ps = p;
-        for (int off = 32; off > 0; off >>= 1) ps += __shfl_xor(ps, off, 64);
-        l = l * alpha + ps;
-#pragma unroll
-        for (int e = 0; e < E; ++e) acc[e] *= alpha;
-        // weighted V rows: key j's probability and row come from lane j (a
-        // bad page's key contributes its probability to l and zeros to acc)
-        // (lanes past the last key hold probability 0 and row 0, so the keys
-        // go in groups of eight, whose loads are all in flight together)
-        const float pv = vok ? p : 0.0f;
-        const int nk = min(64, hi - kb);
-        for (int j0 = 0; j0 < nk; j0 += 8) {
-            float vv[8][E], pj[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                pj[u] = __shfl(pv, j0 + u, 64);
-                const int32_t rj = __shfl(vrow, j0 + u, 64);
-                const float* vr = vg + ((int64_t)rj * a.hkv + kvh) * D;
-#pragma unroll
-                for (int e = 0; e < E; ++e) vv[u][e] = vr[lane + 64 * e];
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-#pragma unroll
-                for (int e = 0; e < E; ++e) acc[e] = fmaf(pj[u], vv[u][e], acc[e]);
-        }
-        m = m_new;
+        for (int j = 0; j < KJ; ++j)
+            qf[j] = valid ? *reinterpret_cast<const float4*>(q + 16 * j + 4 * grp) : float4{0.0f, 0.0f, 0.0f, 0.0f};
     }
-    const int64_t row = (int64_t)(si.q_start + i) * a.hq + it.head;
-    float* out = reinterpret_cast<float*>(a.out) + row * D;
-    const float inv = l > 0.0f ? 1.0f / l : 0.0f;
+    const int32_t k_first = __builtin_amdgcn_readfirstlane(lo_min & ~(kPage - 1));
+    const int32_t k_last = __builtin_amdgcn_readfirstlane(hi_max);
+    lo_max = __builtin_amdgcn_readfirstlane(lo_max);
+    hi_min = __builtin_amdgcn_readfirstlane(hi_min);
+
+    // ---- steps of this wave: page wave + NW i of the slice's pages ------------
+    const int n_pages = (k_last - k_first + kPage - 1) / kPage;
+    const int my_steps = wave < n_pages ? (n_pages - wave + NW - 1) / NW : 0;
+    const int32_t* bt_first = bt_row + (k_first >> 4);
+    auto load_pages = [&](int first) {  // lane i: the page of step first + i
+        const int pg = wave + NW * (first + lane);
+        return pg < n_pages ? bt_first[pg] : 0;
+    };
+    int32_t pw = load_pages(0);
+    constexpr uint32_t kOutOfRange = 0x80000000u;
+    const size_t page_bytes = (size_t)kPage * a.hkv * D * sizeof(float);
+    const uint32_t row_bytes = (uint32_t)(a.hkv * D * sizeof(float));
+    const uint32_t koff = n * row_bytes + (uint32_t)(kvh * D + 4 * grp) * 4u;
+    const uint32_t voff = 4 * grp * row_bytes + (uint32_t)(kvh * D + 4 * n) * 4u;
+    const char* kbase = reinterpret_cast<const char*>(a.k);
+    const char* vbase = reinterpret_cast<const char*>(a.v);
+    bool page_err = false;
+    uint4 kr[KJ], vr[4][VH];  // K and V of one step
+    // Rows past the slice's last key and pages outside the pool read as zeros
+    // through the buffer range check.
+    auto step_page = [&](int i, uint32_t& nrec) -> size_t {
+        const int32_t page = __builtin_amdgcn_readlane(pw, i & 63);
+        const bool ok = (uint32_t)page < (uint32_t)a.num_pages;
+        page_err |= !ok;
+        nrec = ok ? (uint32_t)page_bytes : 0u;
+        return ok ? (size_t)page * page_bytes : 0;
+    };
+    auto load_k = [&](int i) {
+        if (i > 0 && (i & 63) == 0) pw = load_pages(i);
+        uint32_t nrec;
+        const size_t pofs = step_page(i, nrec);
+        const __amdgpu_buffer_rsrc_t rk = page_rsrc(kbase, pofs, nrec);
+        const int32_t left = k_last - (k_first + kPage * (wave + NW * i));  // live keys of the step, if below 16
+        const uint32_t ko = n < left ? koff : kOutOfRange;
 #pragma unroll
-    for (int e = 0; e < E; ++e) out[lane + 64 * e] = acc[e] * inv;
-    if (lane == 0) a.lse[row] = l > 0.0f ? m + logf(l) : kNegInf;
+        for (int j = 0; j < KJ; ++j) kr[j] = load16_at(rk, ko + 64 * j);
+    };
+    auto load_v = [&](int i) {  // after load_k(i): the page window holds step i
+        uint32_t nrec;
+        const size_t pofs = step_page(i, nrec);
+        const __amdgpu_buffer_rsrc_t rv = page_rsrc(vbase, pofs, nrec);
+        const int32_t left = k_last - (k_first + kPage * (wave + NW * i));
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const uint32_t vo = 4 * grp + c < left ? voff + c * row_bytes : kOutOfRange;
+#pragma unroll
+            for (int h = 0; h < VH; ++h) vr[c][h] = load16_at(rv, vo + 256 * h);
+        }
+    };
+
+    float m = kNegInf, l = 0.0f;
+    f32x4 o[VH][4];
+#pragma unroll
+    for (int h = 0; h < VH; ++h)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[h][e] = f32x4{0, 0, 0, 0};
+    // scores of step i against this lane's row, hidden keys -inf; returns whether no key of the step is hidden
+    auto scores = [&](int i, f32x4& s) {
+        const int32_t k0 = k_first + kPage * (wave + NW * i);
+        f32x4 sa = {0, 0, 0, 0}, sb = {0, 0, 0, 0};  // two chains
+#pragma unroll
+        for (int j = 0; j < KJ; j += 2) {
+            const float4 ka = __builtin_bit_cast(float4, kr[j]), kb = __builtin_bit_cast(float4, kr[j + 1]);
+            sa = mfma4(ka.x, qf[j].x, sa);
+            sb = mfma4(kb.x, qf[j + 1].x, sb);
+            sa = mfma4(ka.y, qf[j].y, sa);
+            sb = mfma4(kb.y, qf[j + 1].y, sb);
+            sa = mfma4(ka.z, qf[j].z, sa);
+            sb = mfma4(kb.z, qf[j + 1].z, sb);
+            sa = mfma4(ka.w, qf[j].w, sa);
+            sb = mfma4(kb.w, qf[j + 1].w, sb);
+        }
+        s = sa + sb;
+        const bool full = k0 >= lo_max && k0 + kPage <= hi_min;
+        if (!full) {
+            const int32_t lo_r = lo - (k0 + 4 * grp), hi_r = hi - (k0 + 4 * grp);
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (!(c >= lo_r && c < hi_r)) s[c] = kNegInf;
+        }
+        return full;
+    };
+    // probabilities against this lane's reference; s * scale is taken in two
+    // parts, so that no rounding of the scale enters the exponent (both parts
+    // are positive: hidden keys stay at -inf)
+    auto probs = [&](const f32x4& s) {
+        const float mu = m == kNegInf ? 0.0f : m;
+        f32x4 p;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) p[c] = fast_exp2(fmaf(s[c], a.scale_lo, fmaf(s[c], a.scale_hi, -mu)));
+        return p;
+    };
+    bool by_key = false;  // wave-uniform: a value that is not finite in a step with hidden keys
+    // Steps: V is requested before the scores, which cover its latency, the
+    // next step's K before the weighted values, which cover that one: one
+    // register copy of each, so that three waves fit a SIMD at D = 128.
+    if (my_steps > 0) load_k(0);
+    for (int i = 0; i < my_steps; ++i) {
+        load_v(i);
+        f32x4 s;
+        const bool full = scores(i, s);
+        if (i + 1 < my_steps) load_k(i + 1);
+        if (!full) {
+            uint32_t top = 0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+#pragma unroll
+                for (int h = 0; h < VH; ++h) {
+                    const uint4 w = vr[c][h];
+                    top = max(max(top, max(w.x & 0x7fffffffu, w.y & 0x7fffffffu)),
+                              max(w.z & 0x7fffffffu, w.w & 0x7fffffffu));
+                }
+            by_key |= __builtin_amdgcn_ballot_w64(top >= 0x7f800000u) != 0;
+        }
+        // lazy reference, as in softmax_update
+        const float mx = rg.max(fmax_num(fmax_num(s[0], s[1]), fmax_num(s[2], s[3]))) * a.scale_hi;
+        if (__builtin_amdgcn_ballot_w64(mx > m + kLazy) != 0) {
+            const float m_new = fmax_num(m, mx);
+            const float alpha = fast_exp2(m - (m_new == kNegInf ? 0.0f : m_new));
+            m = m_new;
+            l *= alpha;
+#pragma unroll
+            for (int h = 0; h < VH; ++h)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[h][e] *= alpha;
+        }
+        const f32x4 p = probs(s);
+        l += (p[0] + p[1]) + (p[2] + p[3]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int h = 0; h < VH; ++h) {
+                const float4 vv = __builtin_bit_cast(float4, vr[c][h]);
+                o[h][0] = mfma4(vv.x, p[c], o[h][0]);
+                o[h][1] = mfma4(vv.y, p[c], o[h][1]);
+                o[h][2] = mfma4(vv.z, p[c], o[h][2]);
+                o[h][3] = mfma4(vv.w, p[c], o[h][3]);
+            }
+    }
+    if (__builtin_expect(by_key, 0)) {
+        // An infinite or NaN value must not reach the rows its key is hidden
+        // from, and 0 * inf on the matrix unit would: the weighted values again,
+        // key by key over the keys each row sees, against the final reference.
+#pragma unroll
+        for (int h = 0; h < VH; ++h)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[h][e] = f32x4{0, 0, 0, 0};
+        pw = load_pages(0);
+        for (int i = 0; i < my_steps; ++i) {
+            load_k(i);
+            f32x4 s;
+            (void)scores(i, s);
+            const f32x4 p = probs(s);
+            const int32_t k0 = k_first + kPage * (wave + NW * i);
+            uint32_t nrec;
+            const size_t pofs = step_page(i, nrec);
+            const __amdgpu_buffer_rsrc_t rv = page_rsrc(vbase, pofs, nrec);
+#pragma unroll 1
+            for (int t = 0; t < kPage; ++t) {
+                const float pt = (t & 2) ? ((t & 1) ? p[3] : p[2]) : ((t & 1) ? p[1] : p[0]);
+                const float pk = __shfl(pt, 16 * (t >> 2) + n, 64);
+                if (k0 + t < lo || k0 + t >= hi) continue;
+                const uint32_t vo = t * row_bytes + (uint32_t)(kvh * D + 16 * grp) * 4u;
+#pragma unroll
+                for (int h = 0; h < VH; ++h)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {  // dims 64 h + 16 grp + 4 q + e
+                        const float4 vv = __builtin_bit_cast(float4, load16_at(rv, vo + 256 * h + 16 * q));
+                        o[h][0][q] = fmaf(pk, vv.x, o[h][0][q]);
+                        o[h][1][q] = fmaf(pk, vv.y, o[h][1][q]);
+                        o[h][2][q] = fmaf(pk, vv.z, o[h][2][q]);
+                        o[h][3][q] = fmaf(pk, vv.w, o[h][3][q]);
+                    }
+            }
+        }
+    }
+    if (page_err && lane == 0) atomicOr(a.err, MSTAR_DEVERR_PAGE_RANGE_BIT);
+
+    // ---- combine the waves: each scales its block to the common reference ------
+    l = rg.sum(l);
+    if (grp == 0) {
+        ml_lds[0][wave][n] = m;
+        ml_lds[1][wave][n] = l;
+    }
+    __syncthreads();
+    float mstar = kNegInf, L = 0.0f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) mstar = fmax_num(mstar, ml_lds[0][w][n]);
+    const float mu = mstar == kNegInf ? 0.0f : mstar;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) L += fast_exp2(ml_lds[0][w][n] - mu) * ml_lds[1][w][n];
+    const float scale = fast_exp2(m - mu) * (L > 0.0f ? 1.0f / L : 0.0f);
+    if (wave < n_pages) {  // waves without a step hold nothing
+#pragma unroll
+        for (int h = 0; h < VH; ++h)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                *reinterpret_cast<f32x4*>(&o_lds[wave][n * D + 64 * h + 16 * grp + 4 * i]) =
+                    f32x4{o[h][0][i], o[h][1][i], o[h][2][i], o[h][3][i]} * scale;
+    }
+    __syncthreads();
+    const int nw = min(n_pages, NW);
+    for (int e = thread_id(); e < np * (D / 4); e += 64 * NW) {
+        f32x4 val = *reinterpret_cast<const f32x4*>(&o_lds[0][4 * e]);
+        for (int w = 1; w < nw; ++w) val += *reinterpret_cast<const f32x4*>(&o_lds[w][4 * e]);
+        const int r = p0 + e / (D / 4);
+        const int64_t row = (int64_t)(si.q_start + it.row0 + r / G) * a.hq + kvh * G + r % G;
+        *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(a.out) + row * D + 4 * (e % (D / 4))) = val;
+    }
+    if (wave == 0 && grp == 0 && valid)
+        a.lse[(int64_t)(si.q_start + qi) * a.hq + head] = L > 0.0f ? fmaf(mstar, kLn2, logf(L)) : kNegInf;
 }
 
 // ---------------------------------------------------------------------------
@@ -1375,9 +1564,9 @@ hipError_t launch_few(const KArgs& a, int head_dim, int rb, hipStream_t s) {
 hipError_t launch_f32(const KArgs& a, int head_dim, hipStream_t s) {
     if (a.n_items == 0) return hipSuccess;
     if (head_dim == 64)
-        hipLaunchKernelGGL(f32_kernel<64>, dim3(a.n_items), dim3(256), 0, s, a);
+        hipLaunchKernelGGL((f32_kernel<64, kF32Waves>), dim3(a.n_items), dim3(64 * kF32Waves), 0, s, a);
     else
-        hipLaunchKernelGGL(f32_kernel<128>, dim3(a.n_items), dim3(256), 0, s, a);
+        hipLaunchKernelGGL((f32_kernel<128, kF32Waves>), dim3(a.n_items), dim3(64 * kF32Waves), 0, s, a);
     return hipGetLastError();
 }
 

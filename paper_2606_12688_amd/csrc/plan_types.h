@@ -10,7 +10,8 @@ constexpr int kTileRows = 128;     // query rows per multi-row tile item
 constexpr int kTileKeys = 64;      // keys per LDS tile in the multi-row kernel
 constexpr int kDecodeMaxRows = 64; // (query row x head) rows a few-row item may hold
 constexpr int kSubKeys = 32;       // keys per wave step in the few-row kernel
-constexpr int kF32Rows = 4;        // query rows per fp32 item (one wave each)
+constexpr int kF32Rows = 16;       // query rows per fp32 item
+constexpr int kF32Waves = 4;       // waves per fp32 workgroup
 constexpr int kAppendRows = 16;    // new K/V rows per KV-append item
 
 // Per request.  Query row i sits at position kv_len - q_len + i; its visible
@@ -23,7 +24,8 @@ struct SeqInfo {
 
 // A unit of work over key range [k_begin, k_end).
 //  multi-row / fp32 items: `head` is a query head; rows row0 .. row0+nrows-1
-//    are query rows of the request.
+//    are query rows of the request.  (The fp32 kernel shares the (row, head)
+//    pairs of a KV head's G items out among them as slices of kF32Rows pairs.)
 //  few-row items: `head` is a KV head; row r in [row0, row0+nrows) stands for
 //    query row r / G and query head head*G + r % G (G = Hq / Hkv).
 // part < 0: write the final out/lse; otherwise write fp32 partials to slots

@@ -605,7 +605,7 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
     std::vector<int64_t> tile_pairs;  // visible pairs of each tile item, for the launch order
     lpt(plan.tiles, true, &tile_pairs);
     lpt(plan.few, false, nullptr);
-    lpt(plan.f32, true, nullptr);
+    lpt(plan.f32, false, nullptr);  // a 16-row slice costs its keys, however many of its rows are filled
 
     // ---- 6. launch order of the multi-row workgroups ----------------------------
     // One workgroup per (tile item, query head); one per cascade item (its rows
