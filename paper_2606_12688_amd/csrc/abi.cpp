@@ -392,6 +392,8 @@ MSTAR_EXPORT int mstar_attn_fwd_timed(const mstar_plan_t* plan, const void* q, c
     a.hq = h.params.num_qo_heads;
     a.hkv = h.params.num_kv_heads;
     a.group = h.group;
+    // exact for the pair indices of a tile item (below 128 * group) up to group 4096
+    a.group_inv = h.group > 1 && h.group <= 4096 ? (uint32_t)((1ull << 32) / (uint32_t)h.group + 1) : 0;
     a.bt_stride = h.params.max_blocks_per_seq;
     a.num_pages = h.params.num_pages;
     a.sm_scale = h.params.sm_scale;

@@ -26,6 +26,7 @@ struct KArgs {
     int32_t n_items;
     int32_t n_wgs;         // multi-row launch: workgroups (a multiple of 8)
     int32_t hq, hkv, group, bt_stride, num_pages;
+    uint32_t group_inv;  // 2^32 / group rounded up (0: group is 1 or too large for the multiply)
     float sm_scale;
     float scale_log2;  // sm_scale * log2(e)
     float scale_hi, scale_lo;  // the same as a sum of two positive parts (fp32 kernel)

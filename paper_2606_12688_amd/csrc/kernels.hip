@@ -135,6 +135,13 @@ __device__ __forceinline__ void row_interval(const KArgs& a, const SeqInfo& si, 
     hi = min(h0, it.k_end);
 }
 
+// p / group of a (query row, head) pair index p of an item: a multiply by the
+// host's reciprocal, exact below 2^32 / group.
+__device__ __forceinline__ int div_group(const KArgs& a, int p) {
+    if (a.group_inv == 0) return a.group == 1 ? p : p / a.group;
+    return (int)(((uint64_t)(uint32_t)p * a.group_inv) >> 32);
+}
+
 // Lazy reference threshold (base-2 units): the online softmax moves its
 // reference max only when a row's max exceeds it by more than this, so
 // probabilities taken against a stale reference stay below 2^kLazy.
@@ -354,7 +361,11 @@ constexpr int kTileKeysD128 = MSTAR_TILE_KEYS_D128;
 // softmax's vector work, which bounds d = 64, then has four waves per SIMD to
 // draw from).  BN keys per tile: 64, or 32 (half the LDS and score registers
 // for a third workgroup per CU at d = 128, with a barrier per 32 keys).
-template <int D, int RBW, bool SMALL, bool CASC, int BN>
+// How a workgroup's rows are named: query rows of one head, (query row, head)
+// pairs of a KV head's group, or entries of a cascade's row list.
+enum { kRows, kPacked, kCascade };
+
+template <int D, int RBW, bool SMALL, int MODE, int BN>
 __global__ __launch_bounds__(256, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_kernel(KArgs a) {
     static_assert(BN == 32 || BN == 64, "tile sizes");
     constexpr int NW = 4;            // waves per workgroup (32 rows each)
@@ -384,6 +395,27 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_ke
     const int kvh = head / a.group;
     const WorkItem it = a.items[item];
     const SeqInfo si = a.seqs[it.seq];
+    // Rows of this workgroup: np (query row, head) pairs from pair p0 on, g
+    // heads from head0 on per query row.  A full item gives each head's rows a
+    // workgroup.  The G workgroups of an item that is not full (a request's last
+    // rows, or all of a short one) share its nrows * G pairs out, query row
+    // first, as slices of 64 RBW, the last of which have nothing to do: a
+    // 16-token chunk of 7 heads per KV head fills one slice instead of 16 of
+    // 128 rows in each of seven (48 decode steps, 64 such chunks, one image and
+    // 16 rollouts in one launch: 687 -> 617 us).  Full items keep one head each:
+    // sharing them out as well changes nothing where every row sees the same
+    // keys and costs 2% on causal prompts.  A cascade item names its rows itself.
+    int p0 = 0, np = it.nrows, g = 1, head0 = head;
+    if (MODE == kPacked && it.nrows < 64 * RBW) {
+        g = a.group;
+        head0 = kvh * g;
+        p0 = (head - head0) * 64 * RBW;
+        np = min(it.nrows * g - p0, 64 * RBW);
+        if (np <= 0) return;
+    }
+    auto query_of = [&](int p) -> int {  // query row of pair p: p / g (exact, see group_inv)
+        return MODE != kPacked || g == 1 ? p : (int)(((uint64_t)(uint32_t)p * a.group_inv) >> 32);
+    };
     // the wave index is wave-uniform; readfirstlane lets the compiler keep
     // everything derived from it (row bounds, loop decisions) in scalars
     const int tid = thread_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6) & (NW - 1), lane = tid & 63;
@@ -392,7 +424,7 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_ke
     const RowGroup rg;
 
     // ---- rows owned by this lane ------------------------------------------
-    // CASC (a shared-prefix cascade item): row r is entry row0 + r of the row
+    // kCascade (a shared-prefix cascade item): row r is entry row0 + r of the row
     // list, a (packed query row, query head) of some group member; every key
     // of the item is visible to it.
     int32_t lo[RBW], hi[RBW];  // written to row_lohi, read back on partial tiles
@@ -401,17 +433,18 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_ke
 #pragma unroll
     for (int rb = 0; rb < RBW; ++rb) {
         const int r = wave * 16 * RBW + rb * 16 + n;
-        valid[rb] = r < it.nrows;
+        valid[rb] = r < np;
         lo[rb] = 0;
         hi[rb] = 0;
         int64_t qoff;
-        if constexpr (CASC) {
+        if constexpr (MODE == kCascade) {
             if (valid[rb]) hi[rb] = it.k_end;
             const int32_t e = valid[rb] ? it.row0 + r : it.row0;
             qoff = ((int64_t)a.rows[2 * e] * a.hq + a.rows[2 * e + 1]) * D;
         } else {
-            if (valid[rb]) row_interval(a, si, it, it.row0 + r, lo[rb], hi[rb]);
-            qoff = ((int64_t)(si.q_start + it.row0 + r) * a.hq + head) * D;
+            const int qr = query_of(p0 + r);
+            if (valid[rb]) row_interval(a, si, it, it.row0 + qr, lo[rb], hi[rb]);
+            qoff = ((int64_t)(si.q_start + it.row0 + qr) * a.hq + head0 + (p0 + r - qr * g)) * D;
         }
 #pragma unroll
         for (int s = 0; s < DS; ++s) {
@@ -429,16 +462,27 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_ke
     }
     // wave-uniform bounds: intervals never shrink from one row to the next
     const int wr0 = wave * 16 * RBW;
-    const int wr1 = min(wr0 + 16 * RBW - 1, it.nrows - 1);
-    const bool wave_active = wr0 < it.nrows;
+    const int wr1 = min(wr0 + 16 * RBW - 1, np - 1);
+    const bool wave_active = wr0 < np;
     int32_t w_lo_min = 0, w_lo_max = 0, w_hi_min = 0, w_hi_max = 0;
     if (wave_active) {
-        if constexpr (CASC) {
+        if constexpr (MODE == kCascade) {
             w_hi_min = w_hi_max = it.k_end;  // lo = 0 for every row
         } else {
-            row_interval(a, si, it, it.row0 + wr0, w_lo_min, w_hi_min);
-            row_interval(a, si, it, it.row0 + wr1, w_lo_max, w_hi_max);
+            row_interval(a, si, it, it.row0 + query_of(p0 + wr0), w_lo_min, w_hi_min);
+            row_interval(a, si, it, it.row0 + query_of(p0 + wr1), w_lo_max, w_hi_max);
         }
+    }
+    // Keys of this workgroup's rows.  k_begin needs no row bounds (the window
+    // alone moves it), so that the page indices can be requested beside them;
+    // the loads themselves may run up to the item's end.
+    const int32_t k_end = it.k_end;
+    int32_t k_begin = it.k_begin, rows_end = it.k_end;
+    if (MODE == kPacked && g > 1) {
+        const int32_t first = it.row0 + query_of(p0), last = it.row0 + query_of(p0 + np - 1);
+        if (si.window > 0) k_begin = max(k_begin, (si.kv_len - si.q_len + first - si.window + 1) & ~(kPage - 1));
+        k_begin = __builtin_amdgcn_readfirstlane(k_begin);
+        rows_end = __builtin_amdgcn_readfirstlane(min(it.k_end, a.row_hi[si.hi_off + last]));
     }
 
     float m[RBW], l[RBW];
@@ -485,9 +529,9 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_ke
     // result is first moved.  Load j of wave w fills rows (NW j + w) RPL ..
     // +RPL of the tile, which lie in one page; a thread's slot inside that
     // page and its logical chunk are the same for every tile and every j.
-    const int32_t page0 = it.k_begin >> 4;
-    const int32_t n_pages = ((it.k_end + 15) >> 4) - page0;
-    const int n_tiles = (it.k_end - it.k_begin + BN - 1) / BN;
+    const int32_t page0 = k_begin >> 4;
+    const int32_t n_pages = ((k_end + 15) >> 4) - page0;
+    const int n_tiles = (rows_end - k_begin + BN - 1) / BN;
     const int32_t* bt_item = bt_row + page0;
     // window w of the item's pages: zeros past the last page (range check)
     auto load_window = [&](int w) {
@@ -560,8 +604,8 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_ke
         bool all_ok = true;
 #pragma unroll
         for (int j = 0; j < NLD; ++j) all_ok &= page[j] < (uint32_t)a.num_pages;
-        const int32_t k0 = it.k_begin + tix * BN;
-        const bool tail = k0 + BN > it.k_end;
+        const int32_t k0 = k_begin + tix * BN;
+        const bool tail = k0 + BN > k_end;
         if (__builtin_expect(SMALL && all_ok && !tail, 1)) {
             // common case: only the page offsets change from tile to tile
 #pragma unroll
@@ -575,8 +619,8 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_ke
             for (int j = 0; j < NLD; ++j) {
                 const int pg = ((NW * j + wave) * RPL) >> 4;  // page of this load within the tile
                 const bool ok = page[j] < (uint32_t)a.num_pages;
-                page_err |= !ok && k0 + 16 * pg < it.k_end;
-                const bool live = ok && (!tail || k0 + lrow0 + NW * j * RPL < it.k_end);
+                page_err |= !ok && k0 + 16 * pg < k_end;
+                const bool live = ok && (!tail || k0 + lrow0 + NW * j * RPL < k_end);
                 if (SMALL) {
                     const uint32_t soff = ok ? page[j] * page_bytes : 0u;
                     lds_dma16s(kpool, live ? gk : kOutOfRange, soff, dst + (NW * j + wave) * 1024);
@@ -666,7 +710,7 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_ke
         }
     };
     auto compute_tile = [&](int tix, const char (&cur)[2][TB]) {
-        const int32_t k0 = it.k_begin + tix * BN;
+        const int32_t k0 = k_begin + tix * BN;
         if (!(wave_active && k0 < w_hi_max && k0 + BN > w_lo_min)) return;
         // the compiler's interleaving strategy for LDS reads among MFMAs
         // (1-2% at d = 128, neutral at d = 64)
@@ -742,6 +786,8 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_ke
     if (page_err && lane == 0) atomicOr(a.err, MSTAR_DEVERR_PAGE_RANGE_BIT);
 
     // ---- epilogue -------------------------------------------------------------
+    int pe = p0;  // opaque: the rows' divisions are done again rather than kept through the tile loop
+    asm volatile("" : "+s"(pe));
 #pragma unroll
     for (int rb = 0; rb < RBW; ++rb) {
         const float lt = rg.sum(l[rb]);
@@ -749,7 +795,7 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_ke
         const int r = wave * 16 * RBW + rb * 16 + n;
         const float inv = lt > 0.0f ? 1.0f / lt : 0.0f;
         const float lse = lt > 0.0f ? (m[rb] + __log2f(lt)) * kLn2 : kNegInf;
-        if constexpr (CASC) {
+        if constexpr (MODE == kCascade) {
             const int64_t slot = it.part + r;  // cascade items always write partials
             float* po = a.part_o + slot * D;
 #pragma unroll
@@ -757,7 +803,8 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_ke
                 *reinterpret_cast<f32x4*>(po + db * 16 + 4 * grp) = o[rb][db] * inv;
             if (grp == 0) a.part_lse[slot] = lse;
         } else if (it.part < 0) {
-            const int64_t row = (int64_t)(si.q_start + it.row0 + r) * a.hq + head;
+            const int qr = query_of(pe + r);
+            const int64_t row = (int64_t)(si.q_start + it.row0 + qr) * a.hq + head0 + (pe + r - qr * g);
             bf16_t* out = reinterpret_cast<bf16_t*>(a.out) + row * D;
 #pragma unroll
             for (int db = 0; db < DB; ++db) {
@@ -766,7 +813,8 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_ke
             }
             if (grp == 0) a.lse[row] = lse;
         } else {
-            const int64_t slot = it.part + (int64_t)head * it.head_stride + r;
+            const int qr = query_of(pe + r);
+            const int64_t slot = it.part + (int64_t)(head0 + (pe + r - qr * g)) * it.head_stride + qr;
             float* po = a.part_o + slot * D;
 #pragma unroll
             for (int db = 0; db < DB; ++db)
@@ -1139,12 +1187,12 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 3) void f32_kernel(KArgs a) 
     // ---- this lane's row; the slice's bounds (intervals never shrink) ---------
     const bool valid = n < np;
     const int pr = p0 + (valid ? n : 0);
-    const int qi = it.row0 + pr / G, head = kvh * G + pr % G;
+    const int pq = div_group(a, pr), qi = it.row0 + pq, head = kvh * G + pr - pq * G;
     int32_t lo, hi, lo_min, lo_max, hi_min, hi_max;
     row_interval(a, si, it, qi, lo, hi);
     if (!valid) lo = hi = 0;
-    row_interval(a, si, it, it.row0 + p0 / G, lo_min, hi_min);
-    row_interval(a, si, it, it.row0 + (p0 + np - 1) / G, lo_max, hi_max);
+    row_interval(a, si, it, it.row0 + div_group(a, p0), lo_min, hi_min);
+    row_interval(a, si, it, it.row0 + div_group(a, p0 + np - 1), lo_max, hi_max);
     float4 qf[KJ];
     {
         const float* q = reinterpret_cast<const float*>(a.q) + ((int64_t)(si.q_start + qi) * a.hq + head) * D;
@@ -1362,8 +1410,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 3) void f32_kernel(KArgs a) 
     for (int e = thread_id(); e < np * (D / 4); e += 64 * NW) {
         f32x4 val = *reinterpret_cast<const f32x4*>(&o_lds[0][4 * e]);
         for (int w = 1; w < nw; ++w) val += *reinterpret_cast<const f32x4*>(&o_lds[w][4 * e]);
-        const int r = p0 + e / (D / 4);
-        const int64_t row = (int64_t)(si.q_start + it.row0 + r / G) * a.hq + kvh * G + r % G;
+        const int r = p0 + e / (D / 4), rq = div_group(a, r);
+        const int64_t row = (int64_t)(si.q_start + it.row0 + rq) * a.hq + kvh * G + r - rq * G;
         *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(a.out) + row * D + 4 * (e % (D / 4))) = val;
     }
     if (wave == 0 && grp == 0 && valid)
@@ -1516,35 +1564,35 @@ hipError_t launch_append(const AArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_tiles(const KArgs& a, int head_dim, hipStream_t s) {
-    if (a.n_items == 0) return hipSuccess;
+namespace {
+// both pools within the range of one buffer resource
+bool small_pool(const KArgs& a, int head_dim) {
+    return (uint64_t)a.num_pages * 16 * a.hkv * head_dim * 2 <= kSmallPoolBytes;
+}
+template <int MODE>
+hipError_t launch_tile_mode(const KArgs& a, int head_dim, hipStream_t s) {
     const dim3 g((unsigned)a.n_wgs), b(256);
-    // both pools within the range of one buffer resource
-    const uint64_t pool_bytes = (uint64_t)a.num_pages * 16 * a.hkv * head_dim * 2;
-    const bool small = pool_bytes <= kSmallPoolBytes;
+    const bool small = small_pool(a, head_dim);
     if (head_dim == 64) {
-        if (small) hipLaunchKernelGGL((tile_kernel<64, 2, true, false, 64>), g, b, 0, s, a);
-        else hipLaunchKernelGGL((tile_kernel<64, 2, false, false, 64>), g, b, 0, s, a);
+        if (small) hipLaunchKernelGGL((tile_kernel<64, 2, true, MODE, 64>), g, b, 0, s, a);
+        else hipLaunchKernelGGL((tile_kernel<64, 2, false, MODE, 64>), g, b, 0, s, a);
     } else {
-        if (small) hipLaunchKernelGGL((tile_kernel<128, 2, true, false, kTileKeysD128>), g, b, 0, s, a);
-        else hipLaunchKernelGGL((tile_kernel<128, 2, false, false, kTileKeysD128>), g, b, 0, s, a);
+        if (small) hipLaunchKernelGGL((tile_kernel<128, 2, true, MODE, kTileKeysD128>), g, b, 0, s, a);
+        else hipLaunchKernelGGL((tile_kernel<128, 2, false, MODE, kTileKeysD128>), g, b, 0, s, a);
     }
     return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_tiles(const KArgs& a, int head_dim, hipStream_t s) {
+    if (a.n_items == 0) return hipSuccess;
+    // slices need the division's reciprocal; without grouped heads they are the plain rows
+    return a.group_inv != 0 ? launch_tile_mode<kPacked>(a, head_dim, s) : launch_tile_mode<kRows>(a, head_dim, s);
 }
 
 hipError_t launch_cascade(const KArgs& a, int head_dim, hipStream_t s) {
     if (a.n_items == 0) return hipSuccess;
-    const dim3 g((unsigned)a.n_wgs), b(256);
-    const uint64_t pool_bytes = (uint64_t)a.num_pages * 16 * a.hkv * head_dim * 2;
-    const bool small = pool_bytes <= kSmallPoolBytes;
-    if (head_dim == 64) {
-        if (small) hipLaunchKernelGGL((tile_kernel<64, 2, true, true, 64>), g, b, 0, s, a);
-        else hipLaunchKernelGGL((tile_kernel<64, 2, false, true, 64>), g, b, 0, s, a);
-    } else {
-        if (small) hipLaunchKernelGGL((tile_kernel<128, 2, true, true, kTileKeysD128>), g, b, 0, s, a);
-        else hipLaunchKernelGGL((tile_kernel<128, 2, false, true, kTileKeysD128>), g, b, 0, s, a);
-    }
-    return hipGetLastError();
+    return launch_tile_mode<kCascade>(a, head_dim, s);
 }
 
 hipError_t launch_few(const KArgs& a, int head_dim, int rb, hipStream_t s) {

@@ -25,7 +25,9 @@ struct SeqInfo {
 // A unit of work over key range [k_begin, k_end).
 //  multi-row / fp32 items: `head` is a query head; rows row0 .. row0+nrows-1
 //    are query rows of the request.  (The fp32 kernel shares the (row, head)
-//    pairs of a KV head's G items out among them as slices of kF32Rows pairs.)
+//    pairs of a KV head's G items out among them as slices of kF32Rows pairs,
+//    and the tile kernel those of an item below kTileRows query rows among the
+//    G workgroups of a KV head.)
 //  few-row items: `head` is a KV head; row r in [row0, row0+nrows) stands for
 //    query row r / G and query head head*G + r % G (G = Hq / Hkv).
 // part < 0: write the final out/lse; otherwise write fp32 partials to slots
