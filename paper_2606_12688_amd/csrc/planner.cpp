@@ -614,10 +614,8 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
     // Every workgroup that reads the same K/V pages -- the items of one
     // request and the G query heads of one KV head -- goes to the same XCD,
     // consecutively, so they run together and read each K/V tile from that
-    // L2.  A group costlier than an even share of one XCD is cut into
-    // consecutive runs of items (one such group alone would otherwise leave
-    // the other XCDs idle).  Groups go to the least-loaded XCD, largest first;
-    // inside a group the items keep their order.
+    // L2 (or, where even XCD loads need it, to two or more, a run of
+    // consecutive items on each).  Inside a group the items keep their order.
     auto launch_order = [&](const std::vector<WorkItem>& items, bool per_head, const std::vector<int64_t>* pairs_of,
                             std::vector<int32_t>& order) {
         // groups in order of first appearance; members flat, by group (a counting sort)
@@ -661,47 +659,60 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
                     members[(size_t)fill[gid_of[(size_t)items[i].seq * P.num_kv_heads + kvh]]++] = (int32_t)i;
             }
         }
-        // pieces: whole groups, or consecutive runs of a group costlier than an
-        // even share of one XCD
+        // Costliest first, each group goes to the least-loaded XCD; one that would
+        // take that XCD past an even share is cut there (a run of consecutive
+        // items), and the rest of it is placed in its turn.  Whole groups only
+        // would leave XCDs idle when groups are few: three contexts of 8448, 8192
+        // and 4352 keys over 4 KV heads are 12 groups, which alone load an XCD
+        // with 8448 or 12544 keys (1.20 of the even share): 1200 -> 1050 us for
+        // 4096 queries of each.
         constexpr int kXcds = 8;
         const int64_t share = ceil_div(total, kXcds);
-        struct Piece { int64_t cost, begin, end; int32_t kvh; };
-        std::vector<Piece> pieces;
-        pieces.reserve(ng);
-        for (size_t g = 0; g < ng; ++g) {
-            if (g_cost[g] <= share) {
-                pieces.push_back({g_cost[g], g_off[g], g_off[g + 1], g_kvh[g]});
-                continue;
-            }
-            Piece pc{0, g_off[g], g_off[g], g_kvh[g]};
-            for (int64_t k = g_off[g]; k < g_off[g + 1]; ++k) {
-                const int64_t c = item_cost[(size_t)members[(size_t)k]];
-                if (pc.end > pc.begin && pc.cost + c > share) {
-                    pieces.push_back(pc);
-                    pc = Piece{0, k, k, g_kvh[g]};
-                }
-                pc.end = k + 1;
-                pc.cost += c;
-            }
-            pieces.push_back(pc);
-        }
-        // costliest first, equal costs in creation order (begin grows with it)
-        std::sort(pieces.begin(), pieces.end(), [](const Piece& x, const Piece& y) {
-            return x.cost != y.cost ? x.cost > y.cost : x.begin < y.begin;
-        });
-        // each piece to the least-loaded XCD, then workgroup b of XCD x at launch slot 8 b + x
+        struct Piece { int64_t cost, begin, end; int32_t group; };
+        // a heap's top is the costliest; equal costs in creation order (begin grows with it)
+        auto cheaper = [](const Piece& x, const Piece& y) {
+            return x.cost != y.cost ? x.cost < y.cost : x.begin > y.begin;
+        };
+        std::vector<Piece> todo, pieces;
+        std::vector<int8_t> xcd_of;
+        todo.reserve(ng);
+        pieces.reserve(ng + kXcds);
+        xcd_of.reserve(ng + kXcds);
+        for (size_t g = 0; g < ng; ++g) todo.push_back({g_cost[g], g_off[g], g_off[g + 1], (int32_t)g});
+        std::make_heap(todo.begin(), todo.end(), cheaper);
         const int32_t hpi = per_head ? G : 1;  // workgroups per (item, KV head): its query heads, or the item
-        std::vector<int8_t> xcd_of(pieces.size());
+        std::vector<uint8_t> on_xcd(ng, 0);    // XCDs (bits) that hold a part of the group
         int64_t load[kXcds] = {0, 0, 0, 0, 0, 0, 0, 0};
         size_t count[kXcds] = {0, 0, 0, 0, 0, 0, 0, 0};
-        for (size_t q = 0; q < pieces.size(); ++q) {
-            int x = 0;
-            for (int k = 1; k < kXcds; ++k)
-                if (load[k] < load[x]) x = k;
-            load[x] += pieces[q].cost;
-            count[x] += (size_t)(pieces[q].end - pieces[q].begin) * hpi;
-            xcd_of[q] = (int8_t)x;
+        while (!todo.empty()) {
+            std::pop_heap(todo.begin(), todo.end(), cheaper);
+            Piece pc = todo.back();
+            todo.pop_back();
+            int x = -1;  // least loaded, and without an earlier part of this group while there is one
+            for (int k = 0; k < kXcds; ++k)
+                if ((on_xcd[pc.group] == 0xff || !(on_xcd[pc.group] >> k & 1)) && (x < 0 || load[k] < load[x])) x = k;
+            // up to the even share, to the nearest item; an overrun of 1/64 is not worth a cut
+            if (load[x] + pc.cost > share + share / 64) {
+                int64_t c = 0, k = pc.begin;
+                for (; k < pc.end; ++k) {
+                    const int64_t ci = item_cost[(size_t)members[(size_t)k]];
+                    if (load[x] + c + ci / 2 > share) break;
+                    c += ci;
+                }
+                if (k > pc.begin && k < pc.end) {
+                    todo.push_back({pc.cost - c, k, pc.end, pc.group});
+                    std::push_heap(todo.begin(), todo.end(), cheaper);
+                    pc.cost = c;
+                    pc.end = k;
+                }
+            }
+            load[x] += pc.cost;
+            count[x] += (size_t)(pc.end - pc.begin) * hpi;
+            on_xcd[pc.group] |= (uint8_t)(1 << x);
+            pieces.push_back(pc);
+            xcd_of.push_back((int8_t)x);
         }
+        // workgroup b of XCD x at launch slot 8 b + x
         size_t slots = 0;
         for (int x = 0; x < kXcds; ++x) slots = std::max(slots, count[x]);
         if (slots * kXcds > (size_t)INT32_MAX / 2) return false;
@@ -709,7 +720,7 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
         size_t pos[kXcds] = {0, 0, 0, 0, 0, 0, 0, 0};
         for (size_t q = 0; q < pieces.size(); ++q) {
             const int x = xcd_of[q];
-            const int32_t h0 = pieces[q].kvh * G;  // a cascade item's entry names the KV head's first query head
+            const int32_t h0 = g_kvh[(size_t)pieces[q].group] * G;  // a cascade item's entry names the KV head's first query head
             for (int64_t k = pieces[q].begin; k < pieces[q].end; ++k)
                 for (int32_t h = h0; h < h0 + hpi; ++h) {
                     const size_t b = pos[x]++ * kXcds + x;
