@@ -169,16 +169,14 @@ int hip_fail(hipError_t e, const char* what) {
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Records that `plan`'s device blob is read by work enqueued on `s` (so that a
-// later plan reusing the block waits for it), unless `s` is being captured
-// into a graph: a capture's replays are the caller's to finish before the
-// plan is destroyed.
-hipError_t mark_use(const mstar_plan* plan, hipStream_t s) {
+// The event that marks `plan`'s device blob as read by work enqueued on `s` (a
+// later plan reusing the block waits for it): it goes with the call's last
+// kernel.  NULL while `s` is being captured into a graph: a capture's replays
+// are the caller's to finish before the plan is destroyed.
+hipError_t use_event(const mstar_plan* plan, hipStream_t s, hipEvent_t* ev) {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    hipError_t e = hipStreamIsCapturing(s, &st);
-    if (e != hipSuccess || st != hipStreamCaptureStatusNone) return e;
-    e = hipEventRecord(plan->blk->last_use, s);
-    if (e == hipSuccess) plan->blk->last_use_set = true;
+    const hipError_t e = hipStreamIsCapturing(s, &st);
+    *ev = e == hipSuccess && st == hipStreamCaptureStatusNone ? plan->blk->last_use : nullptr;
     return e;
 }
 
@@ -402,6 +400,12 @@ MSTAR_EXPORT int mstar_attn_fwd_timed(const mstar_plan_t* plan, const void* q, c
     hipStream_t s = stream;
 
     hipError_t e;
+    hipEvent_t use = nullptr;
+    if ((e = use_event(plan, s, &use)) != hipSuccess) return hip_fail(e, "hipStreamIsCapturing");
+    // the kernel class that ends the call carries the use event (none does
+    // when the call ends with the wait for the side stream)
+    const int last = !h.merges.empty() ? 3 : plan->forked ? -1 : !h.f32.empty() ? 2 : !h.cascade.empty() ? 4 : !h.tiles.empty() ? 0 : 1;
+    auto done = [&](int k) { return k == last ? use : nullptr; };
     // The few-row kernel runs on the thread's side stream when the plan also
     // has tile work: it streams K/V from HBM while the tile kernel keeps the
     // matrix units busy.  Both write disjoint outputs and partial slots; the
@@ -424,6 +428,7 @@ MSTAR_EXPORT int mstar_attn_fwd_timed(const mstar_plan_t* plan, const void* q, c
     if (!h.few.empty()) {
         a.items = reinterpret_cast<const mstar::WorkItem*>(blob + plan->off_few);
         a.n_items = (int32_t)h.few.size();
+        a.done = done(1);
         MSTAR_MARK(events_before, 1);
         if ((e = mstar::launch_few(a, D, h.decode_rb, s_few)) != hipSuccess) return hip_fail(e, "few-row kernel launch");
         MSTAR_MARK(events_after, 1);
@@ -436,6 +441,7 @@ MSTAR_EXPORT int mstar_attn_fwd_timed(const mstar_plan_t* plan, const void* q, c
         a.n_items = (int32_t)h.tiles.size();
         a.order = reinterpret_cast<const int32_t*>(blob + plan->off_order);
         a.n_wgs = (int32_t)(h.tile_order.size() / 2);
+        a.done = done(0);
         MSTAR_MARK(events_before, 0);
         if ((e = mstar::launch_tiles(a, D, s)) != hipSuccess) return hip_fail(e, "tile kernel launch");
         MSTAR_MARK(events_after, 0);
@@ -446,6 +452,7 @@ MSTAR_EXPORT int mstar_attn_fwd_timed(const mstar_plan_t* plan, const void* q, c
         a.order = reinterpret_cast<const int32_t*>(blob + plan->off_casc_order);
         a.n_wgs = (int32_t)(h.casc_order.size() / 2);
         a.rows = reinterpret_cast<const int32_t*>(blob + plan->off_casc_rows);
+        a.done = done(4);
         MSTAR_MARK(events_before, 4);
         if ((e = mstar::launch_cascade(a, D, s)) != hipSuccess) return hip_fail(e, "cascade kernel launch");
         MSTAR_MARK(events_after, 4);
@@ -456,6 +463,7 @@ MSTAR_EXPORT int mstar_attn_fwd_timed(const mstar_plan_t* plan, const void* q, c
     if (!h.f32.empty()) {
         a.items = reinterpret_cast<const mstar::WorkItem*>(blob + plan->off_f32);
         a.n_items = (int32_t)h.f32.size();
+        a.done = done(2);
         MSTAR_MARK(events_before, 2);
         if ((e = mstar::launch_f32(a, D, s)) != hipSuccess) return hip_fail(e, "fp32 kernel launch");
         MSTAR_MARK(events_after, 2);
@@ -469,13 +477,15 @@ MSTAR_EXPORT int mstar_attn_fwd_timed(const mstar_plan_t* plan, const void* q, c
         m.lse = lse;
         m.n_items = (int32_t)h.merges.size();
         m.hq = a.hq;
+        m.done = done(3);
         MSTAR_MARK(events_before, 3);
         if ((e = mstar::launch_merge(m, D, h.params.dtype == MSTAR_DTYPE_BF16, s)) != hipSuccess)
             return hip_fail(e, "merge kernel launch");
         MSTAR_MARK(events_after, 3);
     }
 #undef MSTAR_MARK
-    if ((e = mark_use(plan, s)) != hipSuccess) return hip_fail(e, "hipEventRecord(plan use)");
+    if (use && last < 0 && (e = hipEventRecord(use, s)) != hipSuccess) return hip_fail(e, "hipEventRecord(plan use)");
+    if (use) b->last_use_set = true;
     return MSTAR_OK;
 }
 
@@ -525,10 +535,10 @@ MSTAR_EXPORT int mstar_kv_append(const mstar_plan_t* plan, const void* k_new, co
     a.row_bytes = h.params.num_kv_heads * h.params.head_dim * elt;
     a.bt_stride = h.params.max_blocks_per_seq;
     a.num_pages = h.params.num_pages;
-    hipError_t e = mstar::launch_append(a, stream);
-    if (e != hipSuccess) return hip_fail(e, "append kernel launch");
-    if ((e = mark_use(plan, stream)) != hipSuccess)
-        return hip_fail(e, "hipEventRecord(plan use)");
+    hipError_t e = use_event(plan, stream, &a.done);
+    if (e != hipSuccess) return hip_fail(e, "hipStreamIsCapturing");
+    if ((e = mstar::launch_append(a, stream)) != hipSuccess) return hip_fail(e, "append kernel launch");
+    if (a.done) plan->blk->last_use_set = true;
     return MSTAR_OK;
 }
 

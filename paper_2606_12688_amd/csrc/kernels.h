@@ -30,6 +30,7 @@ struct KArgs {
     float sm_scale;
     float scale_log2;  // sm_scale * log2(e)
     float scale_hi, scale_lo;  // the same as a sum of two positive parts (fp32 kernel)
+    hipEvent_t done;  // host side: NULL, or an event that completes with the kernel (not under capture)
 };
 
 struct MArgs {
@@ -40,6 +41,7 @@ struct MArgs {
     float* lse;
     int32_t n_items;
     int32_t hq;
+    hipEvent_t done;  // host side: NULL, or an event that completes with the kernel (not under capture)
 };
 
 struct AArgs {
@@ -54,6 +56,7 @@ struct AArgs {
     int32_t n_items;
     int32_t row_bytes;      // Hkv * head_dim * element size (a multiple of 16)
     int32_t bt_stride, num_pages;
+    hipEvent_t done;  // host side: NULL, or an event that completes with the kernel (not under capture)
 };
 
 hipError_t launch_tiles(const KArgs& a, int head_dim, hipStream_t s);

@@ -16,6 +16,7 @@
 //
 // The softmax runs in base 2: s2 = s * sm_scale * log2(e), p = 2^(s2 - m2),
 // and lse = (m2 + log2 l) * ln 2 at the end.
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -1558,10 +1559,23 @@ __global__ __launch_bounds__(256) void append_kernel(AArgs a) {
 
 }  // namespace
 
+namespace {
+// Launches `kernel`; the event a.done, if given, completes with it.  It rides on
+// the dispatch itself: recorded behind it, it would be a packet of its own that
+// keeps the next kernel waiting (2.9 us a call; each kv_append and fwd marks its
+// plan's use this way).  Not for streams under capture.
+template <typename Args>
+hipError_t launch(void (*kernel)(Args), dim3 grid, dim3 block, const Args& a, hipStream_t s) {
+    void* args[] = {const_cast<Args*>(&a)};
+    const void* fn = reinterpret_cast<const void*>(kernel);
+    return a.done ? hipExtLaunchKernel(fn, grid, block, args, 0, s, nullptr, a.done, 0)
+                  : hipLaunchKernel(fn, grid, block, args, 0, s);
+}
+}  // namespace
+
 hipError_t launch_append(const AArgs& a, hipStream_t s) {
     if (a.n_items == 0) return hipSuccess;
-    hipLaunchKernelGGL(append_kernel, dim3(a.n_items), dim3(256), 0, s, a);
-    return hipGetLastError();
+    return launch(append_kernel, dim3(a.n_items), dim3(256), a, s);
 }
 
 namespace {
@@ -1574,13 +1588,12 @@ hipError_t launch_tile_mode(const KArgs& a, int head_dim, hipStream_t s) {
     const dim3 g((unsigned)a.n_wgs), b(256);
     const bool small = small_pool(a, head_dim);
     if (head_dim == 64) {
-        if (small) hipLaunchKernelGGL((tile_kernel<64, 2, true, MODE, 64>), g, b, 0, s, a);
-        else hipLaunchKernelGGL((tile_kernel<64, 2, false, MODE, 64>), g, b, 0, s, a);
+        if (small) return launch(tile_kernel<64, 2, true, MODE, 64>, g, b, a, s);
+        else return launch(tile_kernel<64, 2, false, MODE, 64>, g, b, a, s);
     } else {
-        if (small) hipLaunchKernelGGL((tile_kernel<128, 2, true, MODE, kTileKeysD128>), g, b, 0, s, a);
-        else hipLaunchKernelGGL((tile_kernel<128, 2, false, MODE, kTileKeysD128>), g, b, 0, s, a);
+        if (small) return launch(tile_kernel<128, 2, true, MODE, kTileKeysD128>, g, b, a, s);
+        else return launch(tile_kernel<128, 2, false, MODE, kTileKeysD128>, g, b, a, s);
     }
-    return hipGetLastError();
 }
 }  // namespace
 
@@ -1599,23 +1612,21 @@ hipError_t launch_few(const KArgs& a, int head_dim, int rb, hipStream_t s) {
     if (a.n_items == 0) return hipSuccess;
     const dim3 g(a.n_items), b(256);
     if (head_dim == 64) {
-        if (rb == 1) hipLaunchKernelGGL((few_kernel<64, 1>), g, b, 0, s, a);
-        else if (rb == 2) hipLaunchKernelGGL((few_kernel<64, 2>), g, b, 0, s, a);
-        else hipLaunchKernelGGL((few_kernel<64, 4>), g, b, 0, s, a);
+        if (rb == 1) return launch(few_kernel<64, 1>, g, b, a, s);
+        else if (rb == 2) return launch(few_kernel<64, 2>, g, b, a, s);
+        else return launch(few_kernel<64, 4>, g, b, a, s);
     } else {  // the planner gives d = 128 units at most 32 rows
-        if (rb == 1) hipLaunchKernelGGL((few_kernel<128, 1>), g, b, 0, s, a);
-        else hipLaunchKernelGGL((few_kernel<128, 2>), g, b, 0, s, a);
+        if (rb == 1) return launch(few_kernel<128, 1>, g, b, a, s);
+        else return launch(few_kernel<128, 2>, g, b, a, s);
     }
-    return hipGetLastError();
 }
 
 hipError_t launch_f32(const KArgs& a, int head_dim, hipStream_t s) {
     if (a.n_items == 0) return hipSuccess;
     if (head_dim == 64)
-        hipLaunchKernelGGL((f32_kernel<64, kF32Waves>), dim3(a.n_items), dim3(64 * kF32Waves), 0, s, a);
+        return launch(f32_kernel<64, kF32Waves>, dim3(a.n_items), dim3(64 * kF32Waves), a, s);
     else
-        hipLaunchKernelGGL((f32_kernel<128, kF32Waves>), dim3(a.n_items), dim3(64 * kF32Waves), 0, s, a);
-    return hipGetLastError();
+        return launch(f32_kernel<128, kF32Waves>, dim3(a.n_items), dim3(64 * kF32Waves), a, s);
 }
 
 hipError_t scratch_buffer(void** ptr) {
@@ -1645,13 +1656,12 @@ hipError_t launch_merge(const MArgs& a, int head_dim, bool bf16_out, hipStream_t
     if (a.n_items == 0) return hipSuccess;
     const dim3 g((a.n_items + 3) / 4), b(256);
     if (head_dim == 64) {
-        if (bf16_out) hipLaunchKernelGGL((merge_kernel<64, true>), g, b, 0, s, a);
-        else hipLaunchKernelGGL((merge_kernel<64, false>), g, b, 0, s, a);
+        if (bf16_out) return launch(merge_kernel<64, true>, g, b, a, s);
+        else return launch(merge_kernel<64, false>, g, b, a, s);
     } else {
-        if (bf16_out) hipLaunchKernelGGL((merge_kernel<128, true>), g, b, 0, s, a);
-        else hipLaunchKernelGGL((merge_kernel<128, false>), g, b, 0, s, a);
+        if (bf16_out) return launch(merge_kernel<128, true>, g, b, a, s);
+        else return launch(merge_kernel<128, false>, g, b, a, s);
     }
-    return hipGetLastError();
 }
 
 }  // namespace mstar
