@@ -829,24 +829,33 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_ke
 // Few-row kernel: one workgroup = up to 16*RB rows (query rows x the query
 // heads of one KV head) against the item's key range.  The four waves take
 // interleaved 32-key steps; K goes straight from HBM into MFMA operand
-// registers, V is staged through a wave-private LDS slice for the transpose
-// read, and the next step's loads are in flight while the current one is
-// computed.  The four waves' partial results are combined through LDS.
+// registers, V straight into a wave-private LDS slot for the transpose read.
+// The four waves' partial results are combined through LDS.
+//
+// Bound: HBM.  One step is in flight per wave: its registers and its V slot take
+// the next step's loads as soon as they are read.  A second set of both bought
+// nothing, since a wave waits for all of its loads before each step (see
+// compute_step), and cost a workgroup per CU and the room beside the tile
+// kernel: 48 decode steps and 64 chunks beside one image and 16 rollouts in
+// one launch 622 -> 574 us, 16 decode steps at D = 64 28.7 -> 27.3, a decode
+// batch of 64 120.5 -> 121.1 (5.1 TB/s either way).
 // ---------------------------------------------------------------------------
 template <int D, int RB>
-__global__ __launch_bounds__(256, RB == 4 ? 1 : 2) void few_kernel(KArgs a) {
+__global__ __launch_bounds__(256, RB == 4 ? 2 : RB == 2 ? 2 : 3) void few_kernel(KArgs a) {
     constexpr int SK = kSubKeys;
     constexpr int RBY = 2 * D;        // bytes per V row in LDS
     constexpr int DS = D / 32, DB = D / 16, CH = D / 8;
     constexpr int VL = SK * CH / 64;  // direct V loads per wave and step
     constexpr int RPL = 64 / CH;      // V rows filled by one wave-wide load
-    constexpr int SB = SK * RBY;      // bytes of one wave's V slot
-    static_assert(RB * 16 * D * 4 <= 4 * SB, "combine buffer must fit in one set of V slots");
-    // V of the steps held in register buffers A and B goes straight from HBM
-    // into wave-private LDS slots, one array per buffer (the wave waits for
-    // all of its loads before each step; see compute_step).
-    __shared__ __attribute__((aligned(1024))) char v_slot_a[4][SB];
-    __shared__ __attribute__((aligned(1024))) char v_slot_b[4][SB];
+    // Bytes of one wave's V slot, a quarter more than it holds: that keeps D =
+    // 128 at three workgroups per CU, which share out a batch cut into 768
+    // pieces better than four do (decode batch of 64: 121 us, against 129 with
+    // four and 512 or 127 with four and 768 pieces; four need 1536 pieces and
+    // their merge for the same 121).
+    constexpr int SB = SK * RBY * 21 / 16;
+    static_assert(RB * 16 * D * 4 <= 4 * SB, "combine buffer must fit in the V slots");
+    static_assert(SB % 256 == 0, "V slots start on a row of LDS banks");
+    __shared__ __attribute__((aligned(1024))) char v_slot[4][SB];
     __shared__ float ml_lds[4][2][RB * 16];
     __shared__ float fin_lds[2][RB * 16];
 
@@ -953,14 +962,16 @@ __global__ __launch_bounds__(256, RB == 4 ? 1 : 2) void few_kernel(KArgs a) {
     const char* kbase = reinterpret_cast<const char*>(a.k);
     const char* vbase = reinterpret_cast<const char*>(a.v);
     bool page_err = false;
-    auto load_step = [&](Step& st, char (&vs)[4][SB], int i) {
+    Step st;
+    __amdgpu_buffer_rsrc_t rv[2];
+    auto load_k = [&](int i) {  // also the step's V pages, for load_v
         if (i > 0 && (i & 31) == 0) {  // next window of page indices
             pw_cur = pw_next;
             pw_next = i + 32 < my_steps ? load_pages(i + 32) : 0;
         }
         const int32_t k0 = it.k_begin + SK * (wave + 4 * i);
         const bool tail = k0 + SK > it.k_end;
-        __amdgpu_buffer_rsrc_t rk[2], rv[2];
+        __amdgpu_buffer_rsrc_t rk[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int32_t page = __builtin_amdgcn_readlane(pw_cur, 2 * (i & 31) + h);
@@ -977,24 +988,26 @@ __global__ __launch_bounds__(256, RB == 4 ? 1 : 2) void few_kernel(KArgs a) {
 #pragma unroll
             for (int s = 0; s < DS; ++s) st.k[kb][s] = load16_at(rk[kb], live ? koff[s] : kOutOfRange);
         }
+    };
+    auto load_v = [&](int i) {
+        const int32_t k0 = it.k_begin + SK * (wave + 4 * i);
+        const bool tail = k0 + SK > it.k_end;
 #pragma unroll
         for (int j = 0; j < VL; ++j) {
             const int row = j * RPL + lane / CH;
             const int h = (j * RPL) >> 4;  // page half of the load's rows: the same across the wave
             const bool live = !tail || k0 + row < it.k_end;
-            lds_load16_nt(rv[h], live ? voff[j % VJ] : kOutOfRange, &vs[wave_u][j * 1024]);
+            lds_load16_nt(rv[h], live ? voff[j % VJ] : kOutOfRange, &v_slot[wave_u][j * 1024]);
         }
     };
 
-    auto compute_step = [&](Step& cur, const char (&vs)[4][SB], int i) {
+    auto compute_step = [&](int i) {
         // Wait for every outstanding load of this wave, K registers and V
-        // slots alike, before the step.  A partial wait that counts the next
-        // step's loads as younger (what the compiler emits, and tighter forms
+        // slot alike, before the step.  A partial wait that counts other
+        // loads as younger (what the compiler emits, and tighter forms
         // of it) has produced stale V on this hardware when direct-to-LDS
         // loads and loads into registers are in flight together, so the
-        // kernel does not rely on their relative completion order.  With
-        // eight waves per CU streaming, the shallower prefetch this leaves
-        // costs about 1% on the decode batch.
+        // kernel does not rely on their relative completion order.
         wait_vmem<0>();
         const int32_t k0 = it.k_begin + SK * (wave + 4 * i);
         f32x4 sc[RB][2];
@@ -1002,11 +1015,12 @@ __global__ __launch_bounds__(256, RB == 4 ? 1 : 2) void few_kernel(KArgs a) {
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
             for (int s = 0; s < DS; ++s) {
-                const bf16x8 kf = __builtin_bit_cast(bf16x8, cur.k[kb][s]);
+                const bf16x8 kf = __builtin_bit_cast(bf16x8, st.k[kb][s]);
 #pragma unroll
                 for (int rb = 0; rb < RB; ++rb)
                     sc[rb][kb] = mfma16(kf, qf[rb][s], s == 0 ? f32x4{0, 0, 0, 0} : sc[rb][kb]);
             }
+        if (i + 1 < my_steps) load_k(i + 1);  // the K registers are free
 
         const bool full = k0 >= lo_max && k0 + SK <= hi_min;
         if (!full) {
@@ -1034,40 +1048,21 @@ __global__ __launch_bounds__(256, RB == 4 ? 1 : 2) void few_kernel(KArgs a) {
         for (int rb = 0; rb < RB; ++rb) pf[rb] = to_bf16x8(sc[rb][0], sc[rb][1]);
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
-            const bf16_t* base = reinterpret_cast<const bf16_t*>(&vs[wave][vrd[db]]);
+            const bf16_t* base = reinterpret_cast<const bf16_t*>(&v_slot[wave][vrd[db]]);
             const bf16x8 vf = cat(lds_read_tr16(base), lds_read_tr16(base + 16 * D));
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) o[rb][db] = mfma16(vf, pf[rb], o[rb][db]);
         }
-        asm volatile("" ::: "memory");
+        // the V slot is free once this wave's reads of it have returned
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (i + 1 < my_steps) load_v(i + 1);
     };
 
-    // Two register buffers: step i computes while step i+1 (and then i+2) is in
-    // flight.  The steady-state loop always issues both loads, so every path
-    // into it has the same loads pending and the compiler waits only for the
-    // buffer it is about to use; the last two or three steps are peeled.
-    Step sa, sb;
-    int i = 0;
-    if (my_steps >= 4) {
-        load_step(sa, v_slot_a, 0);
-        load_step(sb, v_slot_b, 1);
-        do {
-            compute_step(sa, v_slot_a, i);
-            load_step(sa, v_slot_a, i + 2);
-            compute_step(sb, v_slot_b, i + 1);
-            load_step(sb, v_slot_b, i + 3);
-            i += 2;
-        } while (i + 3 < my_steps);
-    } else {
-        if (my_steps > 0) load_step(sa, v_slot_a, 0);
-        if (my_steps > 1) load_step(sb, v_slot_b, 1);
+    if (my_steps > 0) {
+        load_k(0);
+        load_v(0);
     }
-    if (i < my_steps) {
-        compute_step(sa, v_slot_a, i);
-        if (i + 2 < my_steps) load_step(sa, v_slot_a, i + 2);
-    }
-    if (i + 1 < my_steps) compute_step(sb, v_slot_b, i + 1);
-    if (i + 2 < my_steps) compute_step(sa, v_slot_a, i + 2);
+    for (int i = 0; i < my_steps; ++i) compute_step(i);
 
     if (page_err && lane == 0) atomicOr(a.err, MSTAR_DEVERR_PAGE_RANGE_BIT);
 
@@ -1084,7 +1079,7 @@ __global__ __launch_bounds__(256, RB == 4 ? 1 : 2) void few_kernel(KArgs a) {
         }
     }
     __syncthreads();
-    float* obuf = reinterpret_cast<float*>(&v_slot_a[0][0]);
+    float* obuf = reinterpret_cast<float*>(&v_slot[0][0]);
     float scale_own[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {

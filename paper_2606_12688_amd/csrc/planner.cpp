@@ -33,14 +33,18 @@
 #include <cmath>
 #include <cstdio>
 
-// Few-row key pieces are sized to total_keys / MSTAR_FEW_TARGET_ITEMS (at least
-// 256 keys): one round of the 512 workgroup slots of 256 CUs, plus one shorter
-// remainder per unit.  Every split item costs an fp32 partial write and
-// read-back in the merge kernel, so fewer is better once the GPU is full
-// (measured on the decode batch: 512 beats 1024 and 2048).
-#ifndef MSTAR_FEW_TARGET_ITEMS
-#define MSTAR_FEW_TARGET_ITEMS 512
-#endif
+// Few-row key pieces are sized to total_keys / pieces, pieces being one round of
+// the workgroup slots of 256 CUs (three per CU at D = 128, five at D = 64), plus
+// one shorter remainder per unit, and hold at least few_min_keys.  Every
+// split item costs an fp32 partial write and read-back in the merge kernel, so
+// fewer is better once the GPU is full (D = 128, decode batch of 64: 121 us with
+// 768, 129 with 512; D = 64, a batch of 60: 99 us with 1280, 114 with 768, and a
+// batch of 16: 27.4 with pieces of 384 keys, 28.4 with 256 or 640).  Plans whose
+// partials would outgrow the static scratch of the allocation-free entry point
+// take kFewPiecesSmall.
+constexpr int few_pieces(int head_dim) { return head_dim == 64 ? 1280 : 768; }
+constexpr int few_min_keys(int head_dim) { return head_dim == 64 ? 384 : 256; }
+constexpr int kFewPiecesSmall = 512;
 // Cascade items: the shared prefix is cut into chunks until the items reach
 // about this many workgroups.  Every chunk adds an fp32 partial per member row
 // to write and merge (shared-prefix decode: 256 beat 128, 512 and 1024).
@@ -498,9 +502,11 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
     // CUs sharing HBM bandwidth puts this within ~7% of a perfect split, against
     // ~17% for splitting each unit into equal parts).  Tiles are split into
     // equal parts.
-    auto emit = [&](const Unit& u, int32_t chunk, int32_t align, std::vector<WorkItem>& dst, bool few) {
+    // pieces of a unit (nch) and keys of each (cs)
+    auto cut = [&](const Unit& u, int32_t chunk, int32_t align, bool few, int64_t& nch, int64_t& cs) {
         const int64_t n = (int64_t)u.k_end - u.k_begin;
-        int64_t nch = 1, cs = n;
+        nch = 1;
+        cs = n;
         if (chunk > 0 && n > chunk) {
             if (few) {
                 cs = chunk;
@@ -510,8 +516,17 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
             }
             nch = ceil_div(n, cs);
         }
-        // partial slots of a split unit: few-row units [chunk][row]; tile units
-        // [query head][chunk][row]
+    };
+    // partial slots of a split unit: few-row units [chunk][row]; tile units
+    // [query head][chunk][row]
+    auto partial_slots = [&](const Unit& u, int32_t chunk, int32_t align, bool few) -> int64_t {
+        int64_t nch, cs;
+        cut(u, chunk, align, few, nch, cs);
+        return nch > 1 || u.partial ? nch * u.nrows * (few ? 1 : P.num_qo_heads) : 0;
+    };
+    auto emit = [&](const Unit& u, int32_t chunk, int32_t align, std::vector<WorkItem>& dst, bool few) {
+        int64_t nch, cs;
+        cut(u, chunk, align, few, nch, cs);
         const int64_t heads = few ? 1 : P.num_qo_heads;
         for (int64_t c = 0; c < nch; ++c) {
             WorkItem w;
@@ -545,40 +560,49 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
         }
     };
 
-    {  // few-row units: enough items to keep every CU streaming K/V
+    // Keys per piece of the multi-row tiles (0: whole): split only when the tiles
+    // alone cannot fill the GPU.
+    int32_t tile_chunk = 0;
+    {
+        int64_t total = 0;
+        for (const Unit& u : tile_units) total += u.k_end - u.k_begin;
+        if (P.flags & MSTAR_FLAG_FORCE_SPLIT) {
+            tile_chunk = kTileKeys * 2;
+        } else if (!(P.flags & MSTAR_FLAG_NO_SPLIT) && (int64_t)tile_units.size() * P.num_qo_heads < 512 &&
+                   !tile_units.empty()) {
+            int64_t c = std::max<int64_t>(1024, ceil_div(total, 1024));
+            tile_chunk = (int32_t)std::min<int64_t>(ceil_div(c, kTileKeys) * kTileKeys, INT32_MAX / 2);
+        }
+    }
+    // ... and of the few-row units: enough pieces to keep every CU streaming K/V.
+    int32_t few_chunk = 0;
+    if (P.flags & MSTAR_FLAG_FORCE_SPLIT) {
+        few_chunk = kSubKeys * 2;
+    } else if (!(P.flags & MSTAR_FLAG_NO_SPLIT)) {
         int64_t total = 0, longest = 0;
         for (const Unit& u : few_units) {
             total += u.k_end - u.k_begin;
             longest = std::max<int64_t>(longest, u.k_end - u.k_begin);
         }
-        int32_t chunk = 0;
-        if (P.flags & MSTAR_FLAG_FORCE_SPLIT) {
-            chunk = kSubKeys * 2;
-        } else if (!(P.flags & MSTAR_FLAG_NO_SPLIT)) {
-            const int64_t target_items = MSTAR_FEW_TARGET_ITEMS;
-            int64_t c = std::max<int64_t>(256, ceil_div(total, target_items));
-            chunk = (int32_t)std::min<int64_t>(ceil_div(c, 128) * 128, INT32_MAX / 2);
-            // Units that already fill every slot and are within a quarter of
-            // one piece of each other stay whole: splitting would only add a
-            // merge launch (shared-prefix decode without the cascade: 512
-            // units of 4.1-5.1k keys, step 129 -> 120 us).
-            if ((int64_t)few_units.size() >= target_items && longest * 4 <= (int64_t)chunk * 5) chunk = 0;
+        auto chunk_for = [&](int64_t pieces, int64_t least) {
+            const int64_t c = std::max<int64_t>(least, ceil_div(total, pieces));
+            return (int32_t)std::min<int64_t>(ceil_div(c, 128) * 128, INT32_MAX / 2);
+        };
+        const int32_t coarse = chunk_for(kFewPiecesSmall, 256);
+        // Units that already fill the GPU and are within a quarter of one
+        // piece of each other stay whole: splitting would only add a
+        // merge launch (shared-prefix decode without the cascade: 512
+        // units of 4.1-5.1k keys, step 129 -> 120 us).
+        if ((int64_t)few_units.size() < kFewPiecesSmall || longest * 4 > (int64_t)coarse * 5) {
+            few_chunk = chunk_for(few_pieces(P.head_dim), few_min_keys(P.head_dim));
+            int64_t slots = slot;
+            for (const Unit& u : few_units) slots += partial_slots(u, few_chunk, kSubKeys, true);
+            for (const Unit& u : tile_units) slots += partial_slots(u, tile_chunk, kTileKeys, false);
+            if (slots * (P.head_dim + 1) * 4 > MSTAR_NOALLOC_SCRATCH_BYTES - 512) few_chunk = coarse;
         }
-        for (const Unit& u : few_units) emit(u, chunk, kSubKeys, plan.few, true);
     }
-    {  // multi-row tiles: split only when the tiles alone cannot fill the GPU
-        int64_t total = 0;
-        for (const Unit& u : tile_units) total += u.k_end - u.k_begin;
-        int32_t chunk = 0;
-        if (P.flags & MSTAR_FLAG_FORCE_SPLIT) {
-            chunk = kTileKeys * 2;
-        } else if (!(P.flags & MSTAR_FLAG_NO_SPLIT) && (int64_t)tile_units.size() * P.num_qo_heads < 512 &&
-                   !tile_units.empty()) {
-            int64_t c = std::max<int64_t>(1024, ceil_div(total, 1024));
-            chunk = (int32_t)std::min<int64_t>(ceil_div(c, kTileKeys) * kTileKeys, INT32_MAX / 2);
-        }
-        for (const Unit& u : tile_units) emit(u, chunk, kTileKeys, plan.tiles, false);
-    }
+    for (const Unit& u : few_units) emit(u, few_chunk, kSubKeys, plan.few, true);
+    for (const Unit& u : tile_units) emit(u, tile_chunk, kTileKeys, plan.tiles, false);
     plan.partial_slots = slot;
     if (slot > INT32_MAX) { err = "too many partial rows"; return MSTAR_ERR_INVALID_ARG; }
 
