@@ -362,14 +362,19 @@ constexpr int kTileKeysD128 = MSTAR_TILE_KEYS_D128;
 // softmax's vector work, which bounds d = 64, then has four waves per SIMD to
 // draw from).  BN keys per tile: 64, or 32 (half the LDS and score registers
 // for a third workgroup per CU at d = 128, with a barrier per 32 keys).
+// KS > 1: KS groups of four waves take a run of the workgroup's tiles each, with
+// tile buffers of their own, and their results are added up in LDS at the end.
+// For launches that leave a CU at most one workgroup: it then has as many waves
+// as KS workgroups would give it, on a KS-th of the keys.
+//
 // How a workgroup's rows are named: query rows of one head, (query row, head)
 // pairs of a KV head's group, or entries of a cascade's row list.
 enum { kRows, kPacked, kCascade };
 
-template <int D, int RBW, bool SMALL, int MODE, int BN>
-__global__ __launch_bounds__(256, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_kernel(KArgs a) {
+template <int D, int RBW, bool SMALL, int MODE, int BN, int KS>
+__global__ __launch_bounds__(256 * KS, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_kernel(KArgs a) {
     static_assert(BN == 32 || BN == 64, "tile sizes");
-    constexpr int NW = 4;            // waves per workgroup (32 rows each)
+    constexpr int NW = 4;            // waves per key group (32 rows each)
     constexpr int NB = BN / 16;      // 16-key blocks of a tile
     constexpr int NC = BN / 32;      // 32-key steps of the value product
     constexpr int RBY = 2 * D;       // bytes per K/V row in LDS
@@ -380,10 +385,10 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_ke
     constexpr int RPL = 64 / CH;     // rows filled by one wave-wide load
     constexpr int TB = BN * RBY;     // bytes of one K or V tile
     constexpr int PPT = BN / 16;     // pages per tile
-    // two tile buffers: tile t + 1 loads into one while tile t is read from the other
-    __shared__ __attribute__((aligned(1024))) char buf0[2][TB];  // [K, V] of even tiles
-    __shared__ __attribute__((aligned(1024))) char buf1[2][TB];  // [K, V] of odd tiles
-    __shared__ __attribute__((aligned(256))) int32_t page_ring[2][64];
+    // two tile buffers per key group ([K, V] of its even and odd tiles): tile
+    // t + 1 loads into one while tile t is read from the other
+    __shared__ __attribute__((aligned(1024))) char bufs[2][KS][2][TB];
+    __shared__ __attribute__((aligned(256))) int32_t page_rings[KS][2][64];
     // each row's visible interval [lo, hi), read on partial tiles only (kept
     // out of the registers the tile loop carries)
     __shared__ __attribute__((aligned(16))) int2 row_lohi[NW][16 * RBW];
@@ -419,7 +424,12 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_ke
     };
     // the wave index is wave-uniform; readfirstlane lets the compiler keep
     // everything derived from it (row bounds, loop decisions) in scalars
-    const int tid = thread_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6) & (NW - 1), lane = tid & 63;
+    const int tid = thread_id(), lane = tid & 63;
+    const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = wave_all & (NW - 1), kg = KS == 1 ? 0 : wave_all / NW;  // wave within its key group, and the group
+    char (&buf0)[2][TB] = bufs[0][kg];
+    char (&buf1)[2][TB] = bufs[1][kg];
+    int32_t (&page_ring)[2][64] = page_rings[kg];
     const int n = lane & 15, grp = lane >> 4;
     const int32_t* bt_row = a.bt + (int64_t)it.seq * a.bt_stride;
     const RowGroup rg;
@@ -457,7 +467,7 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_ke
             }
         }
     }
-    if (grp == 0) {
+    if (grp == 0 && kg == 0) {
 #pragma unroll
         for (int rb = 0; rb < RBW; ++rb) row_lohi[wave][rb * 16 + n] = make_int2(lo[rb], hi[rb]);
     }
@@ -477,13 +487,21 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_ke
     // Keys of this workgroup's rows.  k_begin needs no row bounds (the window
     // alone moves it), so that the page indices can be requested beside them;
     // the loads themselves may run up to the item's end.
-    const int32_t k_end = it.k_end;
+    int32_t k_end = it.k_end;
     int32_t k_begin = it.k_begin, rows_end = it.k_end;
     if (MODE == kPacked && g > 1) {
         const int32_t first = it.row0 + query_of(p0), last = it.row0 + query_of(p0 + np - 1);
         if (si.window > 0) k_begin = max(k_begin, (si.kv_len - si.q_len + first - si.window + 1) & ~(kPage - 1));
         k_begin = __builtin_amdgcn_readfirstlane(k_begin);
         rows_end = __builtin_amdgcn_readfirstlane(min(it.k_end, a.row_hi[si.hi_off + last]));
+    }
+    // each key group takes an equal run of tiles (the last ones may be empty)
+    const int total_tiles = (rows_end - k_begin + BN - 1) / BN;
+    const int steps = KS == 1 ? total_tiles : (total_tiles + KS - 1) / KS;  // barriers of every wave
+    const int n_tiles = KS == 1 ? total_tiles : min(steps, total_tiles - kg * steps);
+    if constexpr (KS > 1) {
+        k_begin += kg * steps * BN;
+        k_end = min(k_end, k_begin + steps * BN);
     }
 
     float m[RBW], l[RBW];
@@ -532,7 +550,6 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_ke
     // page and its logical chunk are the same for every tile and every j.
     const int32_t page0 = k_begin >> 4;
     const int32_t n_pages = ((k_end + 15) >> 4) - page0;
-    const int n_tiles = (rows_end - k_begin + BN - 1) / BN;
     const int32_t* bt_item = bt_row + page0;
     // window w of the item's pages: zeros past the last page (range check)
     auto load_window = [&](int w) {
@@ -758,7 +775,7 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_ke
         values(vl, pf);
     };
 
-    if (n_tiles > 0) {
+    if (steps > 0) {
         load_window(0);
         load_window(1);
         // The Q fragments are consumed here, so the compiler's wait for their
@@ -768,34 +785,87 @@ __global__ __launch_bounds__(256, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void tile_ke
 #pragma unroll
             for (int s = 0; s < DS; ++s) asm volatile("" ::"v"(qf[rb][s]));
         dma_barrier();  // windows 0 and 1 of the page ring have landed
-        read_pages(0, pv);
-        issue_tile(0, lds_buf0);
+        if (KS == 1 || n_tiles > 0) {
+            read_pages(0, pv);
+            issue_tile(0, lds_buf0);
+        }
         // Tile tix is in buf[tix & 1].  At the top of each tile every wave has
         // its own loads of the tile done (vmcnt) and every wave is done with
         // the other buffer (barrier), which the next tile's loads then take.
-        for (int tix = 0; tix < n_tiles; tix += 2) {
+        for (int tix = 0; tix < steps; tix += 2) {
             dma_barrier();
             if (tix + 1 < n_tiles) issue_tile(tix + 1, lds_buf1);
-            compute_tile(tix, buf0);
-            if (tix + 1 < n_tiles) {
+            if (KS == 1 || tix < n_tiles) compute_tile(tix, buf0);
+            if (tix + 1 < steps) {
                 dma_barrier();
                 if (tix + 2 < n_tiles) issue_tile(tix + 2, lds_buf0);
-                compute_tile(tix + 1, buf1);
+                if (KS == 1 || tix + 1 < n_tiles) compute_tile(tix + 1, buf1);
             }
         }
     }
     if (page_err && lane == 0) atomicOr(a.err, MSTAR_DEVERR_PAGE_RANGE_BIT);
 
     // ---- epilogue -------------------------------------------------------------
+    float lt[RBW];
+#pragma unroll
+    for (int rb = 0; rb < RBW; ++rb) lt[rb] = rg.sum(l[rb]);
+    if constexpr (KS > 1) {
+        // the key groups' results against the largest reference, summed into
+        // group 0 through LDS (the tile buffers are done with)
+        constexpr int R = 64 * RBW;  // rows
+        static_assert(R * D * 4 <= (int)sizeof(bufs), "one group's O^T fits in the tile buffers");
+        float* ml = reinterpret_cast<float*>(&bufs[0][0][0][0]);
+        dma_barrier();
+#pragma unroll
+        for (int rb = 0; rb < RBW; ++rb)
+            if (grp == 0) {
+                ml[(2 * kg) * R + (wave * RBW + rb) * 16 + n] = m[rb];
+                ml[(2 * kg + 1) * R + (wave * RBW + rb) * 16 + n] = lt[rb];
+            }
+        dma_barrier();
+#pragma unroll
+        for (int rb = 0; rb < RBW; ++rb) {
+            const int row = (wave * RBW + rb) * 16 + n;
+            float mstar = kNegInf, L = 0.0f;
+#pragma unroll
+            for (int k = 0; k < KS; ++k) mstar = fmax_num(mstar, ml[2 * k * R + row]);
+            const float mu = mstar == kNegInf ? 0.0f : mstar;
+#pragma unroll
+            for (int k = 0; k < KS; ++k) L += fast_exp2(ml[2 * k * R + row] - mu) * ml[(2 * k + 1) * R + row];
+            const float own = fast_exp2(m[rb] - mu);
+#pragma unroll
+            for (int db = 0; db < DB; ++db) o[rb][db] *= own;
+            m[rb] = mstar;
+            lt[rb] = L;
+        }
+        f32x4* sum = reinterpret_cast<f32x4*>(&bufs[0][0][0][0]);  // [16-byte piece][thread of the group]
+#pragma unroll
+        for (int k = 1; k < KS; ++k) {
+            dma_barrier();
+            if (kg == k) {
+#pragma unroll
+                for (int rb = 0; rb < RBW; ++rb)
+#pragma unroll
+                    for (int db = 0; db < DB; ++db) sum[(rb * DB + db) * 256 + wave * 64 + lane] = o[rb][db];
+            }
+            dma_barrier();
+            if (kg == 0) {
+#pragma unroll
+                for (int rb = 0; rb < RBW; ++rb)
+#pragma unroll
+                    for (int db = 0; db < DB; ++db) o[rb][db] += sum[(rb * DB + db) * 256 + wave * 64 + lane];
+            }
+        }
+        if (kg != 0) return;
+    }
     int pe = p0;  // opaque: the rows' divisions are done again rather than kept through the tile loop
     asm volatile("" : "+s"(pe));
 #pragma unroll
     for (int rb = 0; rb < RBW; ++rb) {
-        const float lt = rg.sum(l[rb]);
         if (!valid[rb]) continue;
         const int r = wave * 16 * RBW + rb * 16 + n;
-        const float inv = lt > 0.0f ? 1.0f / lt : 0.0f;
-        const float lse = lt > 0.0f ? (m[rb] + __log2f(lt)) * kLn2 : kNegInf;
+        const float inv = lt[rb] > 0.0f ? 1.0f / lt[rb] : 0.0f;
+        const float lse = lt[rb] > 0.0f ? (m[rb] + __log2f(lt[rb])) * kLn2 : kNegInf;
         if constexpr (MODE == kCascade) {
             const int64_t slot = it.part + r;  // cascade items always write partials
             float* po = a.part_o + slot * D;
@@ -1578,16 +1648,18 @@ namespace {
 bool small_pool(const KArgs& a, int head_dim) {
     return (uint64_t)a.num_pages * 16 * a.hkv * head_dim * 2 <= kSmallPoolBytes;
 }
-template <int MODE>
+template <int MODE, int KS64, int KS128>
 hipError_t launch_tile_mode(const KArgs& a, int head_dim, hipStream_t s) {
-    const dim3 g((unsigned)a.n_wgs), b(256);
+    const dim3 g((unsigned)a.n_wgs);
     const bool small = small_pool(a, head_dim);
     if (head_dim == 64) {
-        if (small) return launch(tile_kernel<64, 2, true, MODE, 64>, g, b, a, s);
-        else return launch(tile_kernel<64, 2, false, MODE, 64>, g, b, a, s);
+        const dim3 b(256 * KS64);
+        if (small) return launch(tile_kernel<64, 2, true, MODE, 64, KS64>, g, b, a, s);
+        else return launch(tile_kernel<64, 2, false, MODE, 64, KS64>, g, b, a, s);
     } else {
-        if (small) return launch(tile_kernel<128, 2, true, MODE, kTileKeysD128>, g, b, a, s);
-        else return launch(tile_kernel<128, 2, false, MODE, kTileKeysD128>, g, b, a, s);
+        const dim3 b(256 * KS128);
+        if (small) return launch(tile_kernel<128, 2, true, MODE, kTileKeysD128, KS128>, g, b, a, s);
+        else return launch(tile_kernel<128, 2, false, MODE, kTileKeysD128, KS128>, g, b, a, s);
     }
 }
 }  // namespace
@@ -1595,12 +1667,15 @@ hipError_t launch_tile_mode(const KArgs& a, int head_dim, hipStream_t s) {
 hipError_t launch_tiles(const KArgs& a, int head_dim, hipStream_t s) {
     if (a.n_items == 0) return hipSuccess;
     // slices need the division's reciprocal; without grouped heads they are the plain rows
-    return a.group_inv != 0 ? launch_tile_mode<kPacked>(a, head_dim, s) : launch_tile_mode<kRows>(a, head_dim, s);
+    const bool packed = a.group_inv != 0;
+    if (a.key_groups)  // as many groups as the plain instance has workgroups per CU
+        return packed ? launch_tile_mode<kPacked, 4, 3>(a, head_dim, s) : launch_tile_mode<kRows, 4, 3>(a, head_dim, s);
+    return packed ? launch_tile_mode<kPacked, 1, 1>(a, head_dim, s) : launch_tile_mode<kRows, 1, 1>(a, head_dim, s);
 }
 
 hipError_t launch_cascade(const KArgs& a, int head_dim, hipStream_t s) {
     if (a.n_items == 0) return hipSuccess;
-    return launch_tile_mode<kCascade>(a, head_dim, s);
+    return launch_tile_mode<kCascade, 1, 1>(a, head_dim, s);
 }
 
 hipError_t launch_few(const KArgs& a, int head_dim, int rb, hipStream_t s) {

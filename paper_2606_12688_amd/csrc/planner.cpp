@@ -55,6 +55,16 @@ constexpr int kFewPiecesSmall = 512;
 namespace mstar {
 namespace {
 
+constexpr int kCus = 256;
+// Key groups (tile kernel) when the launch leaves each CU at most one workgroup
+// and the longest has at least this many keys: two requests of 1846 tokens, 8/2
+// heads at D = 128 (232 workgroups), 68 -> 50 us; one of 1829 tokens, 16 heads at
+// D = 64, 50 -> 37; 884 and 821 keys: 27 -> 23 and 38 -> 32; 631 keys: 21.5
+// either way; 345 keys: 14.8 -> 15.7.  Past one workgroup per CU the groups'
+// common barriers lose: 300 workgroups of 2422 keys 98 -> 101 us, the 792 of four
+// prompts 60 -> 94.
+constexpr int kGroupKeys = 640;
+
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // The visible interval [lo(i), hi(i)) of every query row of one request: hi
@@ -563,16 +573,29 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
     // Keys per piece of the multi-row tiles (0: whole): split only when the tiles
     // alone cannot fill the GPU.
     int32_t tile_chunk = 0;
-    {
-        int64_t total = 0;
-        for (const Unit& u : tile_units) total += u.k_end - u.k_begin;
-        if (P.flags & MSTAR_FLAG_FORCE_SPLIT) {
-            tile_chunk = kTileKeys * 2;
-        } else if (!(P.flags & MSTAR_FLAG_NO_SPLIT) && (int64_t)tile_units.size() * P.num_qo_heads < 512 &&
-                   !tile_units.empty()) {
-            int64_t c = std::max<int64_t>(1024, ceil_div(total, 1024));
-            tile_chunk = (int32_t)std::min<int64_t>(ceil_div(c, kTileKeys) * kTileKeys, INT32_MAX / 2);
+    if (P.flags & MSTAR_FLAG_FORCE_SPLIT) {
+        tile_chunk = kTileKeys * 2;
+    } else if (!(P.flags & MSTAR_FLAG_NO_SPLIT) && (int64_t)tile_units.size() * P.num_qo_heads < 512 &&
+               !tile_units.empty()) {
+        // pieces of at least 1024 keys; when the workgroups number at most one
+        // per CU, as many pieces as leave it so (the kernel then has a CU's
+        // waves share each workgroup's keys, see key_groups)
+        int64_t total = 0, longest = 0;
+        for (const Unit& u : tile_units) {
+            total += u.k_end - u.k_begin;
+            longest = std::max<int64_t>(longest, u.k_end - u.k_begin);
         }
+        auto workgroups = [&](int64_t chunk) {
+            int64_t n = 0;
+            for (const Unit& u : tile_units)
+                n += ceil_div(u.k_end - u.k_begin, chunk) * P.num_kv_heads *
+                     (u.nrows == kTileRows ? G : ceil_div((int64_t)u.nrows * G, kTileRows));
+            return n;
+        };
+        int64_t c = std::max<int64_t>(1024, ceil_div(total, 1024));
+        if (workgroups(longest) <= kCus)
+            while (c < longest && workgroups(c) > kCus) c += std::max<int64_t>(kTileKeys, c / 8);
+        tile_chunk = (int32_t)std::min<int64_t>(ceil_div(c, kTileKeys) * kTileKeys, INT32_MAX / 2);
     }
     // ... and of the few-row units: enough pieces to keep every CU streaming K/V.
     int32_t few_chunk = 0;
@@ -759,6 +782,11 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
         err = "too many tile workgroups";
         return MSTAR_ERR_INVALID_ARG;
     }
+    // At most one tile workgroup per CU, and long ones: a CU's waves share the
+    // workgroup's keys.  (A cascade's chunks of some 450 keys gain nothing.)
+    int64_t longest = 0;
+    for (const WorkItem& w : plan.tiles) longest = std::max<int64_t>(longest, w.k_end - w.k_begin);
+    plan.key_groups = plan.tile_order.size() / 2 <= (size_t)kCus && longest >= kGroupKeys;
     return MSTAR_OK;
 }
 

@@ -32,6 +32,7 @@ struct HostPlan {
     std::vector<WorkItem> cascade;
     std::vector<int32_t> casc_rows;
     std::vector<int32_t> casc_order;
+    bool key_groups = false;  // multi-row kernel: the waves of a CU share each workgroup's keys
     int64_t visible_pairs = 0;
     int64_t partial_slots = 0;
 
@@ -46,6 +47,7 @@ struct HostPlan {
         for (auto* v : {&tiles, &few, &f32, &appends, &cascade}) v->clear();
         seqs.clear();
         merges.clear();
+        key_groups = false;
         visible_pairs = partial_slots = 0;
     }
     // Bytes the vectors hold (their capacity).
