@@ -775,6 +775,14 @@ __global__ __launch_bounds__(256 * KS, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void ti
         values(vl, pf);
     };
 
+    // Longer items first, also within a CU: of the workgroups that share its
+    // SIMDs the one with the most keys ends the launch, so its waves issue first
+    // (four causal prompts of up to 1677 keys: 60.4 -> 57.4 us; launches of
+    // equal items are unchanged).
+    const int32_t span = rows_end - k_begin;
+    if (span > 1536) __builtin_amdgcn_s_setprio(3);
+    else if (span > 1024) __builtin_amdgcn_s_setprio(2);
+    else if (span > 512) __builtin_amdgcn_s_setprio(1);
     if (steps > 0) {
         load_window(0);
         load_window(1);
