@@ -919,27 +919,28 @@ __global__ __launch_bounds__(256 * KS, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void ti
 // batch of 64 120.5 -> 121.1 (5.1 TB/s either way).
 // ---------------------------------------------------------------------------
 template <int D, int RB>
-__global__ __launch_bounds__(256, RB == 4 ? 2 : RB == 2 ? 2 : 3) void few_kernel(KArgs a) {
+__global__ __launch_bounds__(256, RB == 1 ? 3 : 2) void few_kernel(KArgs a) {
+    constexpr int NW = 4;             // waves
     constexpr int SK = kSubKeys;
     constexpr int RBY = 2 * D;        // bytes per V row in LDS
     constexpr int DS = D / 32, DB = D / 16, CH = D / 8;
     constexpr int VL = SK * CH / 64;  // direct V loads per wave and step
     constexpr int RPL = 64 / CH;      // V rows filled by one wave-wide load
     // Bytes of one wave's V slot, a quarter more than it holds: that keeps D =
-    // 128 at three workgroups per CU, which share out a batch cut into 768
-    // pieces better than four do (decode batch of 64: 121 us, against 129 with
-    // four and 512 or 127 with four and 768 pieces; four need 1536 pieces and
-    // their merge for the same 121).
+    // 128 at three workgroups per CU, which share out a batch cut
+    // into 768 pieces better than four do (decode batch of 64: 121 us, against
+    // 129 with four and 512 or 127 with four and 768 pieces; four need 1536
+    // pieces and their merge for the same 121).
     constexpr int SB = SK * RBY * 21 / 16;
-    static_assert(RB * 16 * D * 4 <= 4 * SB, "combine buffer must fit in the V slots");
+    static_assert(16 * D * 4 <= SB, "a wave's V slot takes 16 rows of its results");
     static_assert(SB % 256 == 0, "V slots start on a row of LDS banks");
-    __shared__ __attribute__((aligned(1024))) char v_slot[4][SB];
-    __shared__ float ml_lds[4][2][RB * 16];
+    __shared__ __attribute__((aligned(1024))) char v_slot[NW][SB];
+    __shared__ float ml_lds[NW][2][RB * 16];
     __shared__ float fin_lds[2][RB * 16];
 
     const WorkItem it = a.items[wg_id()];
     const SeqInfo si = a.seqs[it.seq];
-    const int tid = thread_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6) & 3, lane = tid & 63;
+    const int tid = thread_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6) & (NW - 1), lane = tid & 63;
     const int n = lane & 15, grp = lane >> 4;
     const int G = a.group;
     const int kvh = it.head;
@@ -985,17 +986,17 @@ __global__ __launch_bounds__(256, RB == 4 ? 2 : RB == 2 ? 2 : 3) void few_kernel
         for (int db = 0; db < DB; ++db) o[rb][db] = f32x4{0, 0, 0, 0};
     }
 
-    // Wave w takes steps w, w+4, w+8, ... of 32 keys; its i-th step starts at
-    // key k_begin + 32 * (w + 4 i) and spans exactly two pages (k_begin is page
+    // Wave w takes steps w, w + NW, w + 2 NW, ... of 32 keys; its i-th step starts
+    // at key k_begin + 32 * (w + NW i) and spans exactly two pages (k_begin is page
     // aligned).  The page indices of 32 consecutive steps live in one register
     // (lane 2i+h holds half h of step i) and are read back with readlane, so no
     // block-table load sits between a step and its K/V loads.
     const int n_steps = (it.k_end - it.k_begin + SK - 1) / SK;
-    const int my_steps = wave < n_steps ? (n_steps - wave + 3) / 4 : 0;
+    const int my_steps = wave < n_steps ? (n_steps - wave + NW - 1) / NW : 0;
     const int32_t page0 = it.k_begin >> 4;
     const int32_t n_pages = ((it.k_end + 15) >> 4) - page0;
     auto load_pages = [&](int first_step) {
-        const int pg = 2 * (wave + 4 * (first_step + (lane >> 1))) + (lane & 1);
+        const int pg = 2 * (wave + NW * (first_step + (lane >> 1))) + (lane & 1);
         return pg < n_pages ? bt_row[page0 + pg] : 0;
     };
     int32_t pw_cur = load_pages(0), pw_next = my_steps > 32 ? load_pages(32) : 0;
@@ -1047,7 +1048,7 @@ __global__ __launch_bounds__(256, RB == 4 ? 2 : RB == 2 ? 2 : 3) void few_kernel
             pw_cur = pw_next;
             pw_next = i + 32 < my_steps ? load_pages(i + 32) : 0;
         }
-        const int32_t k0 = it.k_begin + SK * (wave + 4 * i);
+        const int32_t k0 = it.k_begin + SK * (wave + NW * i);
         const bool tail = k0 + SK > it.k_end;
         __amdgpu_buffer_rsrc_t rk[2];
 #pragma unroll
@@ -1068,7 +1069,7 @@ __global__ __launch_bounds__(256, RB == 4 ? 2 : RB == 2 ? 2 : 3) void few_kernel
         }
     };
     auto load_v = [&](int i) {
-        const int32_t k0 = it.k_begin + SK * (wave + 4 * i);
+        const int32_t k0 = it.k_begin + SK * (wave + NW * i);
         const bool tail = k0 + SK > it.k_end;
 #pragma unroll
         for (int j = 0; j < VL; ++j) {
@@ -1087,7 +1088,7 @@ __global__ __launch_bounds__(256, RB == 4 ? 2 : RB == 2 ? 2 : 3) void few_kernel
         // loads and loads into registers are in flight together, so the
         // kernel does not rely on their relative completion order.
         wait_vmem<0>();
-        const int32_t k0 = it.k_begin + SK * (wave + 4 * i);
+        const int32_t k0 = it.k_begin + SK * (wave + NW * i);
         f32x4 sc[RB][2];
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
@@ -1144,11 +1145,10 @@ __global__ __launch_bounds__(256, RB == 4 ? 2 : RB == 2 ? 2 : 3) void few_kernel
 
     if (page_err && lane == 0) atomicOr(a.err, MSTAR_DEVERR_PAGE_RANGE_BIT);
 
-    // ---- combine the four waves -------------------------------------------------
+    // ---- combine the waves -------------------------------------------------------
     float lt[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) lt[rb] = rg.sum(l[rb]);
-    __syncthreads();  // every wave is done with its V slots
     if (grp == 0) {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
@@ -1157,55 +1157,51 @@ __global__ __launch_bounds__(256, RB == 4 ? 2 : RB == 2 ? 2 : 3) void few_kernel
         }
     }
     __syncthreads();
-    float* obuf = reinterpret_cast<float*>(&v_slot[0][0]);
-    float scale_own[RB];
+    // one row block at a time: each wave leaves its results, against the common
+    // reference, in its own V slot (16-byte pieces in lane order: no bank
+    // conflicts), and all threads add the waves' pieces up.  (One wave after the
+    // other into row-major sums took 1-2 us more per workgroup: 16 16-token
+    // chunks 40 -> 35 us, a decode batch of 64 121.2 -> 120.2.)
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
         const int row = rb * 16 + n;
         float mstar = kNegInf;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) mstar = fmaxf(mstar, ml_lds[w][0][row]);
+        for (int w = 0; w < NW; ++w) mstar = fmax_num(mstar, ml_lds[w][0][row]);
         const float mu = mstar == kNegInf ? 0.0f : mstar;
-        float L = 0.0f;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) L += fast_exp2(ml_lds[w][0][row] - mu) * ml_lds[w][1][row];
-        scale_own[rb] = fast_exp2(m[rb] - mu);
         if (wave == 0 && grp == 0) {
+            float L = 0.0f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) L += fast_exp2(ml_lds[w][0][row] - mu) * ml_lds[w][1][row];
             fin_lds[0][row] = mstar;
             fin_lds[1][row] = L;
         }
-    }
-    for (int w = 0; w < 4; ++w) {
-        if (wave == w) {
+        const float own = fast_exp2(m[rb] - mu);
+        f32x4* slot = reinterpret_cast<f32x4*>(&v_slot[wave][0]);
+        if (rb > 0) __syncthreads();  // the previous block has been added up
 #pragma unroll
-            for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-                for (int db = 0; db < DB; ++db) {
-                    f32x4* dst = reinterpret_cast<f32x4*>(&obuf[(rb * 16 + n) * D + db * 16 + 4 * grp]);
-                    const f32x4 val = o[rb][db] * scale_own[rb];
-                    *dst = (w == 0) ? val : *dst + val;
-                }
-        }
+        for (int db = 0; db < DB; ++db) slot[db * 64 + lane] = o[rb][db] * own;
         __syncthreads();
-    }
-    constexpr int NV = RB * 16 * D / 4;  // float4 elements of the combined block
-    for (int e = tid; e < NV; e += 256) {
-        const int row = e / (D / 4), d4 = (e % (D / 4)) * 4;
-        if (row >= it.nrows) continue;
-        const float mstar = fin_lds[0][row], L = fin_lds[1][row];
-        const float inv = L > 0.0f ? 1.0f / L : 0.0f;
-        const float lse = L > 0.0f ? (mstar + __log2f(L)) * kLn2 : kNegInf;
-        const f32x4 val = *reinterpret_cast<const f32x4*>(&obuf[row * D + d4]) * inv;
-        const int rr = it.row0 + row;
-        if (it.part < 0) {
-            const int64_t orow = (int64_t)(si.q_start + rr / G) * a.hq + kvh * G + rr % G;
-            *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16_t*>(a.out) + orow * D + d4) =
-                __builtin_convertvector(val, bf16x4);
-            if (d4 == 0) a.lse[orow] = lse;
-        } else {
-            const int64_t slot = it.part + row;
-            *reinterpret_cast<f32x4*>(a.part_o + slot * D + d4) = val;
-            if (d4 == 0) a.part_lse[slot] = lse;
+        for (int e = tid; e < DB * 64; e += 64 * NW) {
+            const int r = rb * 16 + (e & 15), d4 = (e >> 6) * 16 + 4 * ((e >> 4) & 3);
+            if (r >= it.nrows) continue;
+            f32x4 val = reinterpret_cast<const f32x4*>(&v_slot[0][0])[e];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) val += reinterpret_cast<const f32x4*>(&v_slot[w][0])[e];
+            const float L = fin_lds[1][r];
+            val *= L > 0.0f ? 1.0f / L : 0.0f;
+            const float lse = L > 0.0f ? (fin_lds[0][r] + __log2f(L)) * kLn2 : kNegInf;
+            const int rr = it.row0 + r;
+            if (it.part < 0) {
+                const int64_t orow = (int64_t)(si.q_start + rr / G) * a.hq + kvh * G + rr % G;
+                *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16_t*>(a.out) + orow * D + d4) =
+                    __builtin_convertvector(val, bf16x4);
+                if (d4 == 0) a.lse[orow] = lse;
+            } else {
+                const int64_t slot_r = it.part + r;
+                *reinterpret_cast<f32x4*>(a.part_o + slot_r * D + d4) = val;
+                if (d4 == 0) a.part_lse[slot_r] = lse;
+            }
         }
     }
 }

@@ -34,15 +34,20 @@
 #include <cstdio>
 
 // Few-row key pieces are sized to total_keys / pieces, pieces being one round of
-// the workgroup slots of 256 CUs (three per CU at D = 128, five at D = 64), plus
-// one shorter remainder per unit, and hold at least few_min_keys.  Every
-// split item costs an fp32 partial write and read-back in the merge kernel, so
-// fewer is better once the GPU is full (D = 128, decode batch of 64: 121 us with
-// 768, 129 with 512; D = 64, a batch of 60: 99 us with 1280, 114 with 768, and a
-// batch of 16: 27.4 with pieces of 384 keys, 28.4 with 256 or 640).  Plans whose
-// partials would outgrow the static scratch of the allocation-free entry point
-// take kFewPiecesSmall.
-constexpr int few_pieces(int head_dim) { return head_dim == 64 ? 1280 : 768; }
+// the workgroup slots of 256 CUs (by the kernel instance of rb 16-row blocks),
+// plus one shorter remainder per unit, and hold at least few_min_keys keys.
+// Every split item costs an fp32 partial write and read-back in the merge
+// kernel, so fewer is better once the GPU is full (D = 128, decode batch of 64:
+// 121 us with 768, 129 with 512; D = 64, a batch of 60: 99 us with 1280, 114 with
+// 768, and a batch of 16: 27.4 with pieces of 384 keys, 28.4 with 256 or 640; 30
+// 32-token chunks of 64 rows at D = 64: 45 us with 512, 58 with 1280; 16 16-token
+// chunks of 32 rows at D = 128: 31 with 512, 35 with 768).  Plans whose partials
+// would outgrow the static scratch of the allocation-free entry point take
+// kFewPiecesSmall.
+constexpr int few_pieces(int head_dim, int rb) {
+    if (head_dim == 64) return rb == 1 ? 1280 : rb == 2 ? 1024 : 512;
+    return rb == 1 ? 768 : 512;
+}
 constexpr int few_min_keys(int head_dim) { return head_dim == 64 ? 384 : 256; }
 constexpr int kFewPiecesSmall = 512;
 // Cascade items: the shared prefix is cut into chunks until the items reach
@@ -602,8 +607,9 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
     if (P.flags & MSTAR_FLAG_FORCE_SPLIT) {
         few_chunk = kSubKeys * 2;
     } else if (!(P.flags & MSTAR_FLAG_NO_SPLIT)) {
-        int64_t total = 0, longest = 0;
+        int64_t total = 0, longest = 0, shortest = INT64_MAX;
         for (const Unit& u : few_units) {
+            shortest = std::min<int64_t>(shortest, u.k_end - u.k_begin);
             total += u.k_end - u.k_begin;
             longest = std::max<int64_t>(longest, u.k_end - u.k_begin);
         }
@@ -617,7 +623,13 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
         // merge launch (shared-prefix decode without the cascade: 512
         // units of 4.1-5.1k keys, step 129 -> 120 us).
         if ((int64_t)few_units.size() < kFewPiecesSmall || longest * 4 > (int64_t)coarse * 5) {
-            few_chunk = chunk_for(few_pieces(P.head_dim), few_min_keys(P.head_dim));
+            few_chunk = chunk_for(few_pieces(P.head_dim, plan.decode_rb), few_min_keys(P.head_dim));
+            // near-equal units of more than 16 rows (chunks under one window): equal
+            // pieces without a remainder, whose partials would cost more than
+            // its keys (60 16-token chunks over 1040 keys: 80 -> 62 us, 30 of
+            // them 45 -> 43; units of fewer rows lose or gain up to 1 us)
+            if (plan.decode_rb > 1 && shortest * 8 >= longest * 7 && longest > few_chunk)
+                few_chunk = (int32_t)(ceil_div(ceil_div(longest, longest / few_chunk), kSubKeys) * kSubKeys);
             int64_t slots = slot;
             for (const Unit& u : few_units) slots += partial_slots(u, few_chunk, kSubKeys, true);
             for (const Unit& u : tile_units) slots += partial_slots(u, tile_chunk, kTileKeys, false);

@@ -54,3 +54,16 @@ def test_a_plan_that_fits_the_scratch_with_fewer_pieces_gets_fewer():
     assert keys.max() > fine
     assert 0 < pl.workspace_bytes <= SCRATCH
     pl.destroy()
+
+
+@pytest.mark.parametrize("n,whole", [(30, False), (60, True)])
+def test_near_equal_units_of_many_rows_split_evenly(n, whole):
+    """16-token chunks of 32 rows under one window: equal pieces, no short
+    remainder, and none at all once the units alone come close to a round."""
+    b = W.stream_window_bf16(seed=1, n=n)
+    pl = plan_for(b, attn.FLAG_HOST_ONLY)
+    it = pl.items(1)
+    keys = it[:, 5] - it[:, 4]
+    assert (len(it) == 8 * n) == whole
+    assert keys.min() * 4 >= keys.max() * 3
+    pl.destroy()
