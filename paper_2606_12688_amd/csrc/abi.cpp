@@ -5,7 +5,6 @@
 
 #include <algorithm>
 #include <chrono>
-#include <cmath>
 #include <condition_variable>
 #include <cstring>
 #include <deque>
@@ -178,15 +177,6 @@ hipError_t use_event(const mstar_plan* plan, hipStream_t s, hipEvent_t* ev) {
     const hipError_t e = hipStreamIsCapturing(s, &st);
     *ev = e == hipSuccess && st == hipStreamCaptureStatusNone ? plan->blk->last_use : nullptr;
     return e;
-}
-
-// sm_scale * log2(e) as hi + lo, both positive: hi rounded down, lo the rest
-// (at least a tiny part of hi, so that lo * -inf stays -inf).
-void split_scale(float sm_scale, float& hi, float& lo) {
-    const double c = (double)sm_scale * 1.4426950408889634;
-    hi = (float)c;
-    if ((double)hi > c) hi = std::nextafterf(hi, 0.0f);
-    lo = std::max((float)(c - (double)hi), std::max(hi * 0x1p-60f, std::numeric_limits<float>::denorm_min()));
 }
 
 bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
@@ -395,8 +385,7 @@ MSTAR_EXPORT int mstar_attn_fwd_timed(const mstar_plan_t* plan, const void* q, c
     a.bt_stride = h.params.max_blocks_per_seq;
     a.num_pages = h.params.num_pages;
     a.sm_scale = h.params.sm_scale;
-    a.scale_log2 = h.params.sm_scale * 1.4426950408889634f;
-    split_scale(h.params.sm_scale, a.scale_hi, a.scale_lo);
+    a.scale_log2 = std::min(h.params.sm_scale * 1.4426950408889634f, std::numeric_limits<float>::max());
     hipStream_t s = stream;
 
     hipError_t e;

@@ -30,7 +30,6 @@ struct KArgs {
     uint32_t group_inv;  // 2^32 / group rounded up (0: group is 1 or too large for the multiply)
     float sm_scale;
     float scale_log2;  // sm_scale * log2(e)
-    float scale_hi, scale_lo;  // the same as a sum of two positive parts (fp32 kernel)
     hipEvent_t done;  // host side: NULL, or an event that completes with the kernel (not under capture)
 };
 

@@ -1357,14 +1357,16 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 3) void f32_kernel(KArgs a) 
         }
         return full;
     };
-    // probabilities against this lane's reference; s * scale is taken in two
-    // parts, so that no rounding of the scale enters the exponent (both parts
-    // are positive: hidden keys stay at -inf)
+    // Probabilities against this lane's reference m, the largest unscaled score
+    // so far.  The difference is taken before it is scaled: a scaled score is
+    // off by half an ulp, 2^(e - 24) for one near 2^e, and against a reference
+    // rounded on its own that alone takes 2^x past the largest float from
+    // scores of 2^31 on.  Hidden keys stay at -inf.
     auto probs = [&](const f32x4& s) {
         const float mu = m == kNegInf ? 0.0f : m;
         f32x4 p;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) p[c] = fast_exp2(fmaf(s[c], a.scale_lo, fmaf(s[c], a.scale_hi, -mu)));
+        for (int c = 0; c < 4; ++c) p[c] = fast_exp2((s[c] - mu) * a.scale_log2);
         return p;
     };
     bool by_key = false;  // wave-uniform: a value that is not finite in a step with hidden keys
@@ -1389,11 +1391,13 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 3) void f32_kernel(KArgs a) 
                 }
             by_key |= __builtin_amdgcn_ballot_w64(top >= 0x7f800000u) != 0;
         }
-        // lazy reference, as in softmax_update
-        const float mx = rg.max(fmax_num(fmax_num(s[0], s[1]), fmax_num(s[2], s[3]))) * a.scale_hi;
-        if (__builtin_amdgcn_ballot_w64(mx > m + kLazy) != 0) {
+        // The reference follows every growth (no lazy threshold): probabilities
+        // stay at or below 1, so values as large as the type holds do not
+        // overflow, and the rescale is small beside a step's products.
+        const float mx = rg.max(fmax_num(fmax_num(s[0], s[1]), fmax_num(s[2], s[3])));
+        if (__builtin_amdgcn_ballot_w64(mx > m) != 0) {
             const float m_new = fmax_num(m, mx);
-            const float alpha = fast_exp2(m - (m_new == kNegInf ? 0.0f : m_new));
+            const float alpha = fast_exp2((m - (m_new == kNegInf ? 0.0f : m_new)) * a.scale_log2);
             m = m_new;
             l *= alpha;
 #pragma unroll
@@ -1465,8 +1469,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 3) void f32_kernel(KArgs a) 
     for (int w = 0; w < NW; ++w) mstar = fmax_num(mstar, ml_lds[0][w][n]);
     const float mu = mstar == kNegInf ? 0.0f : mstar;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) L += fast_exp2(ml_lds[0][w][n] - mu) * ml_lds[1][w][n];
-    const float scale = fast_exp2(m - mu) * (L > 0.0f ? 1.0f / L : 0.0f);
+    for (int w = 0; w < NW; ++w) L += fast_exp2((ml_lds[0][w][n] - mu) * a.scale_log2) * ml_lds[1][w][n];
+    const float scale = fast_exp2((m - mu) * a.scale_log2) * (L > 0.0f ? 1.0f / L : 0.0f);
     if (wave < n_pages) {  // waves without a step hold nothing
 #pragma unroll
         for (int h = 0; h < VH; ++h)
@@ -1485,7 +1489,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 3) void f32_kernel(KArgs a) 
         *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(a.out) + row * D + 4 * (e % (D / 4))) = val;
     }
     if (wave == 0 && grp == 0 && valid)
-        a.lse[(int64_t)(si.q_start + qi) * a.hq + head] = L > 0.0f ? fmaf(mstar, kLn2, logf(L)) : kNegInf;
+        a.lse[(int64_t)(si.q_start + qi) * a.hq + head] = L > 0.0f ? fmaf(mstar, a.sm_scale, logf(L)) : kNegInf;
 }
 
 // ---------------------------------------------------------------------------

@@ -57,3 +57,43 @@ def test_values_of_hidden_keys_stay_out(d, bad):
     assert not np.isfinite(o[sees]).any()
     assert np.abs(o[~sees] - ro[~sees]).max() <= 1e-5
     assert np.abs(host64(lse) - rl).max() <= 1e-3
+
+
+@pytest.mark.parametrize("scale", [1e3, 1e5, 1e8])
+def test_scores_far_past_the_exponent_of_exp2(scale):
+    """Scores of 1e6 to 1e16: one key takes all of a row's weight, wherever the
+    roundings of the scores lie."""
+    n, d = 300, 64
+    b = W.custom("f32_large_scores", 4, 2, d, [40], [n], [[(0, n, W.SEG_CAUSAL, 0)]], [0], seed=3, dtype="f32")
+    t = W.make_tensors_torch(b, DEV)
+    t["q"] *= scale
+    t["k_pages"] *= scale
+    out, lse = (host64(x) for x in run_gpu(b, t))
+    ro, rl = oracle_of(b, t)
+    q, k = host64(t["q"]), host64(t["k_pages"])[b.block_table[0]].reshape(-1, 2, d)[:n]
+    for i in range(40):
+        for h in range(4):
+            s = np.sort(k[:n - 40 + i + 1, h // 2] @ q[i, h]) * b.sm_scale
+            err = d * 2.0 ** -24 * np.abs(k[:n - 40 + i + 1, h // 2] * q[i, h]).sum(-1).max() * b.sm_scale
+            if s[-1] - s[-2] < 20 + 2 * err:  # not decided within an fp32 dot product's error
+                continue
+            assert np.abs(out[i, h] - ro[i, h]).max() <= 1e-5, (i, h)
+            assert abs(lse[i, h] - rl[i, h]) <= err + 2.0 ** -22 * abs(rl[i, h]), (i, h)
+    assert np.isfinite(out).all() and np.isfinite(lse).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_values_near_the_largest_float(d):
+    """Values of 1e37 under scores that grow along the keys: no sum of weighted
+    values passes the largest float, since no weight passes 1."""
+    n = 300
+    b = W.custom("f32_large_values", 4, 2, d, [40], [n], [[(0, n, W.SEG_CAUSAL, 0)]], [0], seed=4, dtype="f32")
+    t = W.make_tensors_torch(b, DEV)
+    for p in range((n + 15) // 16):
+        t["k_pages"][int(b.block_table[0, p])] *= 1 + 0.2 * p
+    ref, ref_lse = run_gpu(b, t)  # the same weights over values of unit size
+    t["v_pages"] *= 1e37
+    out, lse = run_gpu(b, t)
+    # both round each product and sum once more or less: 300 terms of 2^-24
+    assert np.abs(host64(out) / 1e37 - host64(ref)).max() <= 300 * 2.0 ** -24 * float(t["v_pages"].abs().max()) / 1e37
+    assert np.array_equal(host64(lse), host64(ref_lse))
