@@ -575,72 +575,6 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
         }
     };
 
-    // Keys per piece of the multi-row tiles (0: whole): split only when the tiles
-    // alone cannot fill the GPU.
-    int32_t tile_chunk = 0;
-    if (P.flags & MSTAR_FLAG_FORCE_SPLIT) {
-        tile_chunk = kTileKeys * 2;
-    } else if (!(P.flags & MSTAR_FLAG_NO_SPLIT) && (int64_t)tile_units.size() * P.num_qo_heads < 512 &&
-               !tile_units.empty()) {
-        // pieces of at least 1024 keys; when the workgroups number at most one
-        // per CU, as many pieces as leave it so (the kernel then has a CU's
-        // waves share each workgroup's keys, see key_groups)
-        int64_t total = 0, longest = 0;
-        for (const Unit& u : tile_units) {
-            total += u.k_end - u.k_begin;
-            longest = std::max<int64_t>(longest, u.k_end - u.k_begin);
-        }
-        auto workgroups = [&](int64_t chunk) {
-            int64_t n = 0;
-            for (const Unit& u : tile_units)
-                n += ceil_div(u.k_end - u.k_begin, chunk) * P.num_kv_heads *
-                     (u.nrows == kTileRows ? G : ceil_div((int64_t)u.nrows * G, kTileRows));
-            return n;
-        };
-        int64_t c = std::max<int64_t>(1024, ceil_div(total, 1024));
-        if (workgroups(longest) <= kCus)
-            while (c < longest && workgroups(c) > kCus) c += std::max<int64_t>(kTileKeys, c / 8);
-        tile_chunk = (int32_t)std::min<int64_t>(ceil_div(c, kTileKeys) * kTileKeys, INT32_MAX / 2);
-    }
-    // ... and of the few-row units: enough pieces to keep every CU streaming K/V.
-    int32_t few_chunk = 0;
-    if (P.flags & MSTAR_FLAG_FORCE_SPLIT) {
-        few_chunk = kSubKeys * 2;
-    } else if (!(P.flags & MSTAR_FLAG_NO_SPLIT)) {
-        int64_t total = 0, longest = 0, shortest = INT64_MAX;
-        for (const Unit& u : few_units) {
-            shortest = std::min<int64_t>(shortest, u.k_end - u.k_begin);
-            total += u.k_end - u.k_begin;
-            longest = std::max<int64_t>(longest, u.k_end - u.k_begin);
-        }
-        auto chunk_for = [&](int64_t pieces, int64_t least) {
-            const int64_t c = std::max<int64_t>(least, ceil_div(total, pieces));
-            return (int32_t)std::min<int64_t>(ceil_div(c, 128) * 128, INT32_MAX / 2);
-        };
-        const int32_t coarse = chunk_for(kFewPiecesSmall, 256);
-        // Units that already fill the GPU and are within a quarter of one
-        // piece of each other stay whole: splitting would only add a
-        // merge launch (shared-prefix decode without the cascade: 512
-        // units of 4.1-5.1k keys, step 129 -> 120 us).
-        if ((int64_t)few_units.size() < kFewPiecesSmall || longest * 4 > (int64_t)coarse * 5) {
-            few_chunk = chunk_for(few_pieces(P.head_dim, plan.decode_rb), few_min_keys(P.head_dim));
-            // near-equal units of more than 16 rows (chunks under one window): equal
-            // pieces without a remainder, whose partials would cost more than
-            // its keys (60 16-token chunks over 1040 keys: 80 -> 62 us, 30 of
-            // them 45 -> 43; units of fewer rows lose or gain up to 1 us)
-            if (plan.decode_rb > 1 && shortest * 8 >= longest * 7 && longest > few_chunk)
-                few_chunk = (int32_t)(ceil_div(ceil_div(longest, longest / few_chunk), kSubKeys) * kSubKeys);
-            int64_t slots = slot;
-            for (const Unit& u : few_units) slots += partial_slots(u, few_chunk, kSubKeys, true);
-            for (const Unit& u : tile_units) slots += partial_slots(u, tile_chunk, kTileKeys, false);
-            if (slots * (P.head_dim + 1) * 4 > MSTAR_NOALLOC_SCRATCH_BYTES - 512) few_chunk = coarse;
-        }
-    }
-    for (const Unit& u : few_units) emit(u, few_chunk, kSubKeys, plan.few, true);
-    for (const Unit& u : tile_units) emit(u, tile_chunk, kTileKeys, plan.tiles, false);
-    plan.partial_slots = slot;
-    if (slot > INT32_MAX) { err = "too many partial rows"; return MSTAR_ERR_INVALID_ARG; }
-
     // ---- 5. longest first ------------------------------------------------------
     auto visible_in = [&](const WorkItem& w) -> int64_t {
         return iv[w.seq].pairs(w.row0, w.row0 + w.nrows, w.k_begin, w.k_end);
@@ -661,10 +595,6 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
             for (size_t i = 0; i < key.size(); ++i) (*keys)[i] = key[i].first;
         }
     };
-    std::vector<int64_t> tile_pairs;  // visible pairs of each tile item, for the launch order
-    lpt(plan.tiles, true, &tile_pairs);
-    lpt(plan.few, false, nullptr);
-    lpt(plan.f32, false, nullptr);  // a 16-row slice costs its keys, however many of its rows are filled
 
     // ---- 6. launch order of the multi-row workgroups ----------------------------
     // One workgroup per (tile item, query head); one per cascade item (its rows
@@ -797,16 +727,143 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
         }
         return true;
     };
-    if (!launch_order(plan.tiles, true, &tile_pairs, plan.tile_order) ||
-        !launch_order(plan.cascade, false, nullptr, plan.casc_order)) {
+
+    // ---- 7. pieces of the few-row units: enough to keep every CU streaming K/V ------
+    int32_t few_chunk = 0, few_coarse = 0;  // keys per piece; the same if partials outgrow the static scratch
+    if (P.flags & MSTAR_FLAG_FORCE_SPLIT) {
+        few_chunk = kSubKeys * 2;
+    } else if (!(P.flags & MSTAR_FLAG_NO_SPLIT)) {
+        int64_t total = 0, longest = 0, shortest = INT64_MAX;
+        for (const Unit& u : few_units) {
+            shortest = std::min<int64_t>(shortest, u.k_end - u.k_begin);
+            total += u.k_end - u.k_begin;
+            longest = std::max<int64_t>(longest, u.k_end - u.k_begin);
+        }
+        auto chunk_for = [&](int64_t pieces, int64_t least) {
+            const int64_t c = std::max<int64_t>(least, ceil_div(total, pieces));
+            return (int32_t)std::min<int64_t>(ceil_div(c, 128) * 128, INT32_MAX / 2);
+        };
+        few_coarse = chunk_for(kFewPiecesSmall, 256);
+        // Units that already fill the GPU and are within a quarter of one
+        // piece of each other stay whole: splitting would only add a
+        // merge launch (shared-prefix decode without the cascade: 512
+        // units of 4.1-5.1k keys, step 129 -> 120 us).
+        if ((int64_t)few_units.size() < kFewPiecesSmall || longest * 4 > (int64_t)few_coarse * 5) {
+            few_chunk = chunk_for(few_pieces(P.head_dim, plan.decode_rb), few_min_keys(P.head_dim));
+            // near-equal units of more than 16 rows (chunks under one window): equal
+            // pieces without a remainder, whose partials would cost more than
+            // its keys (60 16-token chunks over 1040 keys: 80 -> 62 us, 30 of
+            // them 45 -> 43; units of fewer rows lose or gain up to 1 us)
+            if (plan.decode_rb > 1 && shortest * 8 >= longest * 7 && longest > few_chunk)
+                few_chunk = (int32_t)(ceil_div(ceil_div(longest, longest / few_chunk), kSubKeys) * kSubKeys);
+        }
+    }
+    int64_t few_items = 0;
+    for (const Unit& u : few_units) {
+        int64_t nch, cs;
+        cut(u, few_chunk, kSubKeys, true, nch, cs);
+        few_items += nch;
+    }
+
+    // ---- 8. the multi-row items: their pieces, key groups, launch order ------------
+    // Items in pieces of `chunk` keys (0: whole), longest first, and their order;
+    // may be called again with another chunk.
+    std::vector<int64_t> tile_pairs;  // visible pairs of each tile item, for the launch order
+    const size_t merges0 = plan.merges.size();
+    const int64_t slot0 = slot;
+    auto emit_tiles = [&](int32_t chunk) {
+        plan.tiles.clear();
+        plan.merges.resize(merges0);
+        slot = slot0;
+        for (const Unit& u : tile_units) emit(u, chunk, kTileKeys, plan.tiles, false);
+        lpt(plan.tiles, true, &tile_pairs);
+        return launch_order(plan.tiles, true, &tile_pairs, plan.tile_order);
+    };
+    // Key groups (the kernel instance in which a CU's waves share the keys of one
+    // workgroup): when every CU gets at most one workgroup, launch slots that
+    // have nothing to do (each takes a whole CU while it exits) and few-row items
+    // beside the tiles included, and the longest is long.  A key-group
+    // workgroup waits for a CU without any other: one 1829-token prompt, 16/8
+    // heads at D = 64, beside 64 decode steps of 4000 keys 198 us, against 127
+    // without; one of 1000, 16/8 at D = 128, beside 16 of 2000 57 against 53, but
+    // beside one of 1000 40 against 43.
+    const int64_t beside = (P.flags & MSTAR_FLAG_SERIAL) ? 0 : few_items;
+    auto takes_groups = [&] {
+        int64_t longest = 0;
+        for (const WorkItem& w : plan.tiles) longest = std::max<int64_t>(longest, w.k_end - w.k_begin);
+        return (int64_t)plan.tile_order.size() / 2 + beside <= kCus && longest >= kGroupKeys;
+    };
+    bool ok = true, emitted = false;
+    if (P.flags & MSTAR_FLAG_FORCE_SPLIT) {
+        ok = emit_tiles(kTileKeys * 2);
+    } else if ((P.flags & MSTAR_FLAG_NO_SPLIT) || (int64_t)tile_units.size() * P.num_qo_heads >= 512) {
+        ok = emit_tiles(0);  // the tiles alone fill the GPU
+    } else if (!tile_units.empty()) {
+        // Pieces of at least 1024 keys; or fewer and longer ones, at most one
+        // launch slot per CU, for key groups, where those cost less.
+        int64_t total = 0, longest = 0, work = 0;
+        for (const Unit& u : tile_units) {
+            const int64_t n = (int64_t)u.k_end - u.k_begin;
+            total += n;
+            longest = std::max(longest, n);
+            work += n * P.num_kv_heads * (u.nrows == kTileRows ? G : ceil_div((int64_t)u.nrows * G, kTileRows));
+        }
+        auto rounded = [](int64_t c) {
+            return (int32_t)std::min<int64_t>(ceil_div(c, kTileKeys) * kTileKeys, INT32_MAX / 2);
+        };
+        auto launch_slots = [&](int64_t chunk) {
+            int64_t n = 0;
+            for (const Unit& u : tile_units) n += ceil_div((int64_t)u.k_end - u.k_begin, chunk) * P.num_qo_heads;
+            return n;
+        };
+        // Cost in keys that a CU's waves walk together (some 15 us per 1000 at D
+        // = 128, 9 at D = 64): the longest piece with key groups; without, an
+        // even share of the launch or the longest piece walked by its four waves
+        // alone, which takes 1.5 times as long per key.  Partials written and
+        // merged: 75 rows a key, and a launch.  Both sides measured: one causal
+        // request of 640 queries over 20000 keys, 28/4 heads, D = 128, 1024-key
+        // pieces 219 us, whole with groups 269; 1100 over 32000, 16/8, D = 64, 195
+        // and 254; two of 1846 over 1846, 8/2, D = 128, 45 and 35; 256 over 32000,
+        // 59 and 52 (2048-key pieces).
+        auto cost = [&](int32_t chunk, bool groups) {
+            int64_t piece = 0, rows = 0;
+            for (const Unit& u : tile_units) {
+                int64_t nch, cs;
+                cut(u, chunk, kTileKeys, false, nch, cs);
+                piece = std::max(piece, cs);
+                rows += partial_slots(u, chunk, kTileKeys, false);
+            }
+            return (groups ? piece : std::max(work / kCus, piece + piece / 2)) + (rows > 0 ? 400 + rows / 75 : 0);
+        };
+        const int64_t base = std::max<int64_t>(1024, ceil_div(total, 1024));
+        // Longer pieces without key groups in the end would only be slower (640
+        // queries over 8000 keys 185 us, 15 requests of 20 over 8000 121; in
+        // 1024-key pieces 106 and 95).
+        if (longest >= kGroupKeys && launch_slots(longest) + beside <= kCus) {
+            int64_t c = base;
+            while (c < longest && launch_slots(c) + beside > kCus) c += std::max<int64_t>(kTileKeys, c / 8);
+            if (rounded(c) > rounded(base) && cost(rounded(c), true) < cost(rounded(base), false))
+                emitted = emit_tiles(rounded(c)) && takes_groups();  // padding of the order may still be in the way
+        }
+        if (!emitted) ok = emit_tiles(rounded(base));
+    }
+    if (!ok || !launch_order(plan.cascade, false, nullptr, plan.casc_order)) {
         err = "too many tile workgroups";
         return MSTAR_ERR_INVALID_ARG;
     }
-    // At most one tile workgroup per CU, and long ones: a CU's waves share the
-    // workgroup's keys.  (A cascade's chunks of some 450 keys gain nothing.)
-    int64_t longest = 0;
-    for (const WorkItem& w : plan.tiles) longest = std::max<int64_t>(longest, w.k_end - w.k_begin);
-    plan.key_groups = plan.tile_order.size() / 2 <= (size_t)kCus && longest >= kGroupKeys;
+    plan.key_groups = takes_groups();
+
+    // ---- 9. the few-row items -------------------------------------------------------
+    if (few_chunk != 0 && !(P.flags & MSTAR_FLAG_FORCE_SPLIT)) {
+        int64_t slots = slot;
+        for (const Unit& u : few_units) slots += partial_slots(u, few_chunk, kSubKeys, true);
+        if (slots * (P.head_dim + 1) * 4 > MSTAR_NOALLOC_SCRATCH_BYTES - 512) few_chunk = few_coarse;
+    }
+    for (const Unit& u : few_units) emit(u, few_chunk, kSubKeys, plan.few, true);
+    plan.partial_slots = slot;
+    if (slot > INT32_MAX) { err = "too many partial rows"; return MSTAR_ERR_INVALID_ARG; }
+    lpt(plan.few, false, nullptr);
+    lpt(plan.f32, false, nullptr);  // a 16-row slice costs its keys, however many of its rows are filled
     return MSTAR_OK;
 }
 
