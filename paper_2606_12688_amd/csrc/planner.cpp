@@ -42,8 +42,8 @@
 // 768, and a batch of 16: 27.4 with pieces of 384 keys, 28.4 with 256 or 640; 30
 // 32-token chunks of 64 rows at D = 64: 45 us with 512, 58 with 1280; 16 16-token
 // chunks of 32 rows at D = 128: 31 with 512, 35 with 768).  Plans whose partials
-// would outgrow the static scratch of the allocation-free entry point take
-// kFewPiecesSmall.
+// fit the static scratch of the allocation-free entry point with kFewPiecesSmall
+// only take that.
 constexpr int few_pieces(int head_dim, int rb) {
     if (head_dim == 64) return rb == 1 ? 1280 : rb == 2 ? 1024 : 512;
     return rb == 1 ? 768 : 512;
@@ -729,7 +729,7 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
     };
 
     // ---- 7. pieces of the few-row units: enough to keep every CU streaming K/V ------
-    int32_t few_chunk = 0, few_coarse = 0;  // keys per piece; the same if partials outgrow the static scratch
+    int32_t few_chunk = 0, few_coarse = 0;  // keys per piece; the same where only these partials fit the static scratch
     if (P.flags & MSTAR_FLAG_FORCE_SPLIT) {
         few_chunk = kSubKeys * 2;
     } else if (!(P.flags & MSTAR_FLAG_NO_SPLIT)) {
@@ -855,9 +855,12 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
 
     // ---- 9. the few-row items -------------------------------------------------------
     if (few_chunk != 0 && !(P.flags & MSTAR_FLAG_FORCE_SPLIT)) {
-        int64_t slots = slot;
-        for (const Unit& u : few_units) slots += partial_slots(u, few_chunk, kSubKeys, true);
-        if (slots * (P.head_dim + 1) * 4 > MSTAR_NOALLOC_SCRATCH_BYTES - 512) few_chunk = few_coarse;
+        auto in_scratch = [&](int32_t chunk) {
+            int64_t slots = slot;
+            for (const Unit& u : few_units) slots += partial_slots(u, chunk, kSubKeys, true);
+            return slots * (P.head_dim + 1) * 4 <= MSTAR_NOALLOC_SCRATCH_BYTES - 512;
+        };
+        if (!in_scratch(few_chunk) && in_scratch(few_coarse)) few_chunk = few_coarse;
     }
     for (const Unit& u : few_units) emit(u, few_chunk, kSubKeys, plan.few, true);
     plan.partial_slots = slot;

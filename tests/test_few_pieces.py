@@ -56,6 +56,23 @@ def test_a_plan_that_fits_the_scratch_with_fewer_pieces_gets_fewer():
     pl.destroy()
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_a_plan_past_the_scratch_either_way_keeps_its_pieces(d):
+    """Decode steps beside a 1200-token chunk over 60000 keys, whose own partials
+    take hundreds of megabytes: fewer few-row pieces would not make them fit."""
+    q, kv = [1] * 64, [4000] * 64
+    keys = []
+    for n in (0, 1):
+        q, kv = q + [1200] * n, kv + [60000] * n
+        b = W.custom("past", 28, 4, d, q, kv, [[(0, x, W.SEG_CAUSAL, 0)] for x in kv], [0] * len(q))
+        pl = plan_for(b, attn.FLAG_HOST_ONLY)
+        it = pl.items(1)
+        keys.append(sorted((it[:, 5] - it[:, 4]).tolist()))
+        assert (pl.workspace_bytes > SCRATCH) == bool(n)
+        pl.destroy()
+    assert keys[0] == keys[1]
+
+
 @pytest.mark.parametrize("n,whole", [(30, False), (60, True)])
 def test_near_equal_units_of_many_rows_split_evenly(n, whole):
     """16-token chunks of 32 rows under one window: equal pieces, no short
