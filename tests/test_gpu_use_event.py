@@ -21,15 +21,45 @@ KINDS = {"tiles": ("text_latent_bf16", attn.FLAG_NO_SPLIT, False), "few": ("deco
          "append": ("decode_bf16", attn.FLAG_NO_SPLIT, False)}
 
 
+def _other(name):
+    """Another batch for the same buffer whose work list differs: where the seed
+    does not change it, one of a little less work."""
+    if name == "text_latent_bf16":
+        return W.text_latent_bf16(7, n=2, text=29, latent=290)
+    if name == "tiny_causal_f32":
+        lens = [int(n) - 1 for n in W.reduced(name).seqs[:, 1]]
+        return W.custom("tiny_other", 2, 1, 64, lens, lens, [[(0, n, W.SEG_CAUSAL, 0)] for n in lens], [0] * len(lens),
+                        dtype="f32")
+    if name == "shared_prefix_decode_bf16":
+        return W.shared_prefix_decode_bf16(7, n=36, prefix=320, own_min=1, own_max=150, hq=8, hkv=2)
+    return W.reduced(name, seed=7)
+
+
+def _work(b, flags, cascade):
+    """The items of every kind of a plan whose device buffer has the smallest size."""
+    pl = plan_for(b, flags | attn.FLAG_HOST_ONLY, cascade=cascade)
+    assert pl.stats()["device_bytes"] <= 64 << 10
+    lists = [pl.items(k) for k in range(5)]
+    pl.destroy()
+    return lists
+
+
 @pytest.mark.parametrize("kind", list(KINDS))
 def test_next_plan_waits_for_the_last_kernel(kind):
     import torch
 
     name, flags, cascade = KINDS[kind]
     b = W.reduced(name)
+    other = _other(name)
+    mine, others = (_work(x, flags, cascade) for x in (b, other))
+    # the items that the call's last kernels read (the append's follow from the requests)
+    last = {"tiles": 0, "few": 1, "f32": 2, "merge": 3, "cascade": 3, "forked": 1}
+    if kind == "append":
+        assert (b.seqs != other.seqs).any()
+    else:
+        assert not np.array_equal(mine[last[kind]], others[last[kind]])
     t = W.make_tensors_torch(b, DEV)
     ref, ref_lse = run_gpu(b, t, flags, cascade=cascade)
-    other = W.reduced(name, seed=7)
     stream, upload = torch.cuda.current_stream(), torch.cuda.Stream()
     bt = torch.from_numpy(np.ascontiguousarray(b.block_table)).to(DEV)
     out, lse = torch.zeros_like(ref), torch.zeros_like(ref_lse)
