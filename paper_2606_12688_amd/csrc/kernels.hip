@@ -495,6 +495,17 @@ __global__ __launch_bounds__(256 * KS, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void ti
         k_begin = __builtin_amdgcn_readfirstlane(k_begin);
         rows_end = __builtin_amdgcn_readfirstlane(min(it.k_end, a.row_hi[si.hi_off + last]));
     }
+    // Workgroups with more keys first, also within a CU: of those that share its
+    // SIMDs the one with the most ends the launch, so its waves issue first, by
+    // quarters of the launch's longest (four causal prompts of up to 1677 keys:
+    // 60.4 -> 57.4 us; launches of equal items are unchanged).  With key groups a
+    // CU has one workgroup, whose groups wait for each other.
+    if constexpr (KS == 1) {
+        const int32_t span = rows_end - k_begin;
+        if (span > 3 * a.quarter_span) __builtin_amdgcn_s_setprio(3);
+        else if (span > 2 * a.quarter_span) __builtin_amdgcn_s_setprio(2);
+        else if (span > a.quarter_span) __builtin_amdgcn_s_setprio(1);
+    }
     // each key group takes an equal run of tiles (the last ones may be empty)
     const int total_tiles = (rows_end - k_begin + BN - 1) / BN;
     const int steps = KS == 1 ? total_tiles : (total_tiles + KS - 1) / KS;  // barriers of every wave
@@ -775,14 +786,6 @@ __global__ __launch_bounds__(256 * KS, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void ti
         values(vl, pf);
     };
 
-    // Longer items first, also within a CU: of the workgroups that share its
-    // SIMDs the one with the most keys ends the launch, so its waves issue first
-    // (four causal prompts of up to 1677 keys: 60.4 -> 57.4 us; launches of
-    // equal items are unchanged).
-    const int32_t span = rows_end - k_begin;
-    if (span > 1536) __builtin_amdgcn_s_setprio(3);
-    else if (span > 1024) __builtin_amdgcn_s_setprio(2);
-    else if (span > 512) __builtin_amdgcn_s_setprio(1);
     if (steps > 0) {
         load_window(0);
         load_window(1);

@@ -788,10 +788,13 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
     // without; one of 1000, 16/8 at D = 128, beside 16 of 2000 57 against 53, but
     // beside one of 1000 40 against 43.
     const int64_t beside = (P.flags & MSTAR_FLAG_SERIAL) ? 0 : few_items;
+    auto longest_of = [](const std::vector<WorkItem>& items) {
+        int32_t n = 0;
+        for (const WorkItem& w : items) n = std::max(n, w.k_end - w.k_begin);
+        return n;
+    };
     auto takes_groups = [&] {
-        int64_t longest = 0;
-        for (const WorkItem& w : plan.tiles) longest = std::max<int64_t>(longest, w.k_end - w.k_begin);
-        return (int64_t)plan.tile_order.size() / 2 + beside <= kCus && longest >= kGroupKeys;
+        return (int64_t)plan.tile_order.size() / 2 + beside <= kCus && longest_of(plan.tiles) >= kGroupKeys;
     };
     bool ok = true, emitted = false;
     if (P.flags & MSTAR_FLAG_FORCE_SPLIT) {
@@ -852,6 +855,8 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
         return MSTAR_ERR_INVALID_ARG;
     }
     plan.key_groups = takes_groups();
+    plan.tile_span = longest_of(plan.tiles);
+    plan.casc_span = longest_of(plan.cascade);
 
     // ---- 9. the few-row items -------------------------------------------------------
     if (few_chunk != 0 && !(P.flags & MSTAR_FLAG_FORCE_SPLIT)) {

@@ -32,6 +32,7 @@ struct HostPlan {
     std::vector<WorkItem> cascade;
     std::vector<int32_t> casc_rows;
     std::vector<int32_t> casc_order;
+    int32_t tile_span = 0, casc_span = 0;  // keys of the longest multi-row and cascade item
     bool key_groups = false;  // multi-row kernel: the waves of a CU share each workgroup's keys
     int64_t visible_pairs = 0;
     int64_t partial_slots = 0;
@@ -47,6 +48,7 @@ struct HostPlan {
         for (auto* v : {&tiles, &few, &f32, &appends, &cascade}) v->clear();
         seqs.clear();
         merges.clear();
+        tile_span = casc_span = 0;
         key_groups = false;
         visible_pairs = partial_slots = 0;
     }
