@@ -431,7 +431,7 @@ MSTAR_EXPORT int mstar_attn_fwd_timed(const mstar_plan_t* plan, const void* q, c
         a.order = reinterpret_cast<const int32_t*>(blob + plan->off_order);
         a.n_wgs = (int32_t)(h.tile_order.size() / 2);
         a.key_groups = h.key_groups;
-        a.quarter_span = h.tile_span / 4;
+        a.span_step = std::max(512, h.tile_span / 4);
         a.done = done(0);
         MSTAR_MARK(events_before, 0);
         if ((e = mstar::launch_tiles(a, D, s)) != hipSuccess) return hip_fail(e, "tile kernel launch");
@@ -443,7 +443,7 @@ MSTAR_EXPORT int mstar_attn_fwd_timed(const mstar_plan_t* plan, const void* q, c
         a.order = reinterpret_cast<const int32_t*>(blob + plan->off_casc_order);
         a.n_wgs = (int32_t)(h.casc_order.size() / 2);
         a.key_groups = 0;
-        a.quarter_span = h.casc_span / 4;
+        a.span_step = std::max(512, h.casc_span / 4);
         a.rows = reinterpret_cast<const int32_t*>(blob + plan->off_casc_rows);
         a.done = done(4);
         MSTAR_MARK(events_before, 4);

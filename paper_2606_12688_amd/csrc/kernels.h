@@ -26,7 +26,7 @@ struct KArgs {
     int32_t n_items;
     int32_t n_wgs;         // multi-row launch: workgroups (a multiple of 8)
     int32_t key_groups;    // multi-row launch: 1 if a workgroup splits its keys over groups of waves
-    int32_t quarter_span;  // multi-row launch: a quarter of the longest item's keys
+    int32_t span_step;     // multi-row launch: keys per step of wave priority
     int32_t hq, hkv, group, bt_stride, num_pages;
     uint32_t group_inv;  // 2^32 / group rounded up (0: group is 1 or too large for the multiply)
     float sm_scale;

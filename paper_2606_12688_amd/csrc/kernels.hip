@@ -498,13 +498,16 @@ __global__ __launch_bounds__(256 * KS, D == 64 ? 4 : (BN == 32 ? 3 : 2)) void ti
     // Workgroups with more keys first, also within a CU: of those that share its
     // SIMDs the one with the most ends the launch, so its waves issue first, by
     // quarters of the launch's longest (four causal prompts of up to 1677 keys:
-    // 60.4 -> 57.4 us; launches of equal items are unchanged).  With key groups a
-    // CU has one workgroup, whose groups wait for each other.
+    // 60.4 -> 57.4 us, of 2000-8000 679 -> 671 against steps of 512 keys; one of
+    // 12000 319 -> 321; equal items are unchanged) but at least 512 keys: with
+    // lower steps 67 short rollouts, 275 and 422 keys at D = 64, take 104.9 us for
+    // 102.4.  With key groups a CU has one workgroup, whose groups wait for each
+    // other.
     if constexpr (KS == 1) {
         const int32_t span = rows_end - k_begin;
-        if (span > 3 * a.quarter_span) __builtin_amdgcn_s_setprio(3);
-        else if (span > 2 * a.quarter_span) __builtin_amdgcn_s_setprio(2);
-        else if (span > a.quarter_span) __builtin_amdgcn_s_setprio(1);
+        if (span > 3 * a.span_step) __builtin_amdgcn_s_setprio(3);
+        else if (span > 2 * a.span_step) __builtin_amdgcn_s_setprio(2);
+        else if (span > a.span_step) __builtin_amdgcn_s_setprio(1);
     }
     // each key group takes an equal run of tiles (the last ones may be empty)
     const int total_tiles = (rows_end - k_begin + BN - 1) / BN;
