@@ -526,7 +526,7 @@ MSTAR_EXPORT int mstar_kv_append(const mstar_plan_t* plan, const void* k_new, co
     a.n_items = (int32_t)h.appends.size();
     const int elt = h.params.dtype == MSTAR_DTYPE_BF16 ? 2 : 4;
     a.row_bytes = h.params.num_kv_heads * h.params.head_dim * elt;
-    a.new_bytes = 2 * (int64_t)h.row_hi.size() * a.row_bytes;  // row_hi: an entry per query row
+    a.new_bytes = 2 * (int64_t)h.row_hi.size() * a.row_bytes;  // row_hi: an entry per query row, padded to eight
     a.bt_stride = h.params.max_blocks_per_seq;
     a.num_pages = h.params.num_pages;
     hipError_t e = use_event(plan, stream, &a.done);

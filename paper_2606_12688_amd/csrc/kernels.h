@@ -56,7 +56,7 @@ struct AArgs {
     int32_t* err;           // sticky device error word
     int32_t n_items;
     int32_t row_bytes;      // Hkv * head_dim * element size (a multiple of 16)
-    int64_t new_bytes;      // K and V rows of the step together
+    int64_t new_bytes;      // K and V rows of the step together (up to seven rows more)
     int32_t bt_stride, num_pages;
     hipEvent_t done;  // host side: NULL, or an event that completes with the kernel (not under capture)
 };

@@ -932,7 +932,7 @@ __global__ __launch_bounds__(256, RB == 1 ? 3 : 2) void few_kernel(KArgs a) {
     constexpr int DS = D / 32, DB = D / 16, CH = D / 8;
     constexpr int VL = SK * CH / 64;  // direct V loads per wave and step
     constexpr int RPL = 64 / CH;      // V rows filled by one wave-wide load
-    // Bytes of one wave's V slot, a quarter more than it holds: that keeps D =
+    // Bytes of one wave's V slot, 5/16 more than it holds: that keeps D =
     // 128 at three workgroups per CU, which share out a batch cut
     // into 768 pieces better than four do (decode batch of 64: 121 us, against
     // 129 with four and 512 or 127 with four and 768 pieces; four need 1536
