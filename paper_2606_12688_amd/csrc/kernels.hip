@@ -1228,14 +1228,17 @@ __global__ __launch_bounds__(256, RB == 1 ? 3 : 2) void few_kernel(KArgs a) {
 // 4 n).  K and V go straight into registers; nothing passes through LDS but
 // the combine.
 //
-// Bound: the fp32 matrix rate (64 MFMAs of 32 cycles per 16 rows x 16 keys at
-// D = 128) once a few hundred items are in flight, latency below that.  One
-// wave per (row, head) with scalar dot products, each reading all of its keys
-// by itself, took 350 us where this takes 40 us (four prompts of 246-782
-// tokens and four decode rows, 8/2 heads, D = 128: 2.3 GFLOP); four prompts of
-// 5-64 tokens at D = 64: 8.1 -> 5.5 us.  Four waves per workgroup: eight have
-// the longest item done sooner, but only one such workgroup fits a CU at D =
-// 128, which bares every item's first loads and its combine (55 us).
+// Bound: latency inside a step, not a rate.  Four prompts of 246-782 tokens and
+// four decode rows (8/2 heads, D = 128: 2.3 GFLOP) keep the matrix units busy
+// 0.30 of the time (64 MFMAs of 32 cycles per 16 rows x 16 keys; the CU with
+// the most has 18 us of them) and read 10 bytes per clock and CU from L2, of
+// about 64; waves spend 0.40 of their time waiting for loads and barriers and
+// 0.47 for an issue slot.  One wave per (row, head) with scalar dot products,
+// each reading all of its keys by itself, took 350 us for it where this takes
+// 41; four prompts of 5-64 tokens at D = 64: 8.1 -> 5.5 us.  Four waves per
+// workgroup: eight have the longest item done sooner, but only one such
+// workgroup fits a CU at D = 128, which bares every item's first loads and its
+// combine (55 us).
 // ---------------------------------------------------------------------------
 template <int D, int NW>
 __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 3) void f32_kernel(KArgs a) {
