@@ -1229,9 +1229,9 @@ __global__ __launch_bounds__(256, RB == 1 ? 3 : 2) void few_kernel(KArgs a) {
 // the combine.
 //
 // Bound: latency inside a step, not a rate.  Four prompts of 246-782 tokens and
-// four decode rows (8/2 heads, D = 128: 2.3 GFLOP) keep the matrix units busy
-// 0.30 of the time (64 MFMAs of 32 cycles per 16 rows x 16 keys; the CU with
-// the most has 18 us of them) and read 10 bytes per clock and CU from L2, of
+// four decode rows (8/2 heads, D = 128: 2.3 GFLOP) keep the matrix units busy a
+// third of the time (64 MFMAs of 32 cycles per 16 rows x 16 keys; the CU with
+// the most has 21 us of them) and read 10-13 bytes per clock and CU from L2, of
 // about 64; waves spend 0.40 of their time waiting for loads and barriers and
 // 0.47 for an issue slot.  One wave per (row, head) with scalar dot products,
 // each reading all of its keys by itself, took 350 us for it where this takes
