@@ -758,12 +758,20 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
                 few_chunk = (int32_t)(ceil_div(ceil_div(longest, longest / few_chunk), kSubKeys) * kSubKeys);
         }
     }
-    int64_t few_items = 0;
+    int64_t few_items = 0, few_keys = 0;
     for (const Unit& u : few_units) {
         int64_t nch, cs;
         cut(u, few_chunk, kSubKeys, true, nch, cs);
         few_items += nch;
+        few_keys += u.k_end - u.k_begin;
     }
+    // whether so many partial rows fit the static scratch of the allocation-free entry point
+    auto in_scratch = [&](int64_t slots) { return slots * (P.head_dim + 1) * 4 <= MSTAR_NOALLOC_SCRATCH_BYTES - 512; };
+    auto few_slots = [&](int32_t chunk) {
+        int64_t n = 0;
+        for (const Unit& u : few_units) n += partial_slots(u, chunk, kSubKeys, true);
+        return n;
+    };
 
     // ---- 8. the multi-row items: their pieces, key groups, launch order ------------
     // Items in pieces of `chunk` keys (0: whole), longest first, and their order;
@@ -779,93 +787,120 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
         lpt(plan.tiles, true, &tile_pairs);
         return launch_order(plan.tiles, true, &tile_pairs, plan.tile_order);
     };
-    // Key groups (the kernel instance in which a CU's waves share the keys of one
-    // workgroup): when every CU gets at most one workgroup, launch slots that
-    // have nothing to do (each takes a whole CU while it exits) and few-row items
-    // beside the tiles included, and the longest is long.  A key-group
-    // workgroup waits for a CU without any other: one 1829-token prompt, 16/8
-    // heads at D = 64, beside 64 decode steps of 4000 keys 198 us, against 127
-    // without; one of 1000, 16/8 at D = 128, beside 16 of 2000 57 against 53, but
-    // beside one of 1000 40 against 43.
-    const int64_t beside = (P.flags & MSTAR_FLAG_SERIAL) ? 0 : few_items;
+    // Where the tiles alone cannot fill the GPU: pieces of at least 1024 keys, or
+    // longer ones, or key groups (the kernel instance in which a CU's waves share
+    // the keys of one workgroup) with pieces as long as they need: at most one
+    // launch slot per CU, also of those that have nothing to do (each holds a
+    // whole CU while it exits).  The choice is by cost, in keys that a CU's waves
+    // walk together (some 15 us per 1000 at D = 128, 9 at D = 64):
+    //  without groups, what the CU with the most workgroups walks, or the longest
+    //  piece walked by its four waves alone, which takes 1.5 times as long per key;
+    //  with groups, the longest piece, and the wait for CUs that few-row items
+    //  beside it hold, the longer the more CUs the two kinds want;
+    //  partials written and merged: 55 rows (70 at D = 64) a key, and a launch.
+    // Longer pieces without groups have to save a tenth (15% at D = 64).
+    //
+    // Measured on 340 launches of 1-3 requests and of many equal ones, with and
+    // without few-row work: time above the better side of each 2.0-2.5% for longer
+    // pieces (never 4.6-6.4%, always 9%), 0.2% (1.5% beside few-row work) for
+    // groups (never 10% and 3%, always 1% and 4%).  For instance (us): 640 queries over
+    // 20000 keys, 28/4 heads, D = 128: 1024-key pieces 219, 6720-key ones 197, whole
+    // with groups 269; 1100 over 32000, 16/8, D = 64: 195, 173 (4608) and 254; two of
+    // 1846 over 1846, 8/2, D = 128: 45, with groups 35; 1829 over 1829, 16/8, D = 64,
+    // beside 64 decode steps of 4000 keys: 127, with groups 198.
     auto longest_of = [](const std::vector<WorkItem>& items) {
         int32_t n = 0;
         for (const WorkItem& w : items) n = std::max(n, w.k_end - w.k_begin);
         return n;
     };
-    auto takes_groups = [&] {
-        return (int64_t)plan.tile_order.size() / 2 + beside <= kCus && longest_of(plan.tiles) >= kGroupKeys;
+    struct Split {  // of all tile units at one piece length
+        int64_t piece = 0, rows = 0;       // longest piece, partial rows
+        int64_t workgroups = 0, slots = 0;  // with rows, and all that are launched
     };
-    bool ok = true, emitted = false;
-    if (P.flags & MSTAR_FLAG_FORCE_SPLIT) {
-        ok = emit_tiles(kTileKeys * 2);
-    } else if ((P.flags & MSTAR_FLAG_NO_SPLIT) || (int64_t)tile_units.size() * P.num_qo_heads >= 512) {
-        ok = emit_tiles(0);  // the tiles alone fill the GPU
-    } else if (!tile_units.empty()) {
-        // Pieces of at least 1024 keys; or fewer and longer ones, at most one
-        // launch slot per CU, for key groups, where those cost less.
-        int64_t total = 0, longest = 0, work = 0;
-        for (const Unit& u : tile_units) {
-            const int64_t n = (int64_t)u.k_end - u.k_begin;
-            total += n;
-            longest = std::max(longest, n);
-            work += n * P.num_kv_heads * (u.nrows == kTileRows ? G : ceil_div((int64_t)u.nrows * G, kTileRows));
-        }
-        auto rounded = [](int64_t c) {
-            return (int32_t)std::min<int64_t>(ceil_div(c, kTileKeys) * kTileKeys, INT32_MAX / 2);
-        };
-        auto launch_slots = [&](int64_t chunk) {
-            int64_t n = 0;
-            for (const Unit& u : tile_units) n += ceil_div((int64_t)u.k_end - u.k_begin, chunk) * P.num_qo_heads;
-            return n;
-        };
-        // Cost in keys that a CU's waves walk together (some 15 us per 1000 at D
-        // = 128, 9 at D = 64): the longest piece with key groups; without, an
-        // even share of the launch or the longest piece walked by its four waves
-        // alone, which takes 1.5 times as long per key.  Partials written and
-        // merged: 75 rows a key, and a launch.  Both sides measured: one causal
-        // request of 640 queries over 20000 keys, 28/4 heads, D = 128, 1024-key
-        // pieces 219 us, whole with groups 269; 1100 over 32000, 16/8, D = 64, 195
-        // and 254; two of 1846 over 1846, 8/2, D = 128, 45 and 35; 256 over 32000,
-        // 59 and 52 (2048-key pieces).
-        auto cost = [&](int32_t chunk, bool groups) {
-            int64_t piece = 0, rows = 0;
-            for (const Unit& u : tile_units) {
-                int64_t nch, cs;
-                cut(u, chunk, kTileKeys, false, nch, cs);
-                piece = std::max(piece, cs);
-                rows += partial_slots(u, chunk, kTileKeys, false);
-            }
-            return (groups ? piece : std::max(work / kCus, piece + piece / 2)) + (rows > 0 ? 400 + rows / 75 : 0);
-        };
-        const int64_t base = std::max<int64_t>(1024, ceil_div(total, 1024));
-        // Longer pieces without key groups in the end would only be slower (640
-        // queries over 8000 keys 185 us, 15 requests of 20 over 8000 121; in
-        // 1024-key pieces 106 and 95).
-        if (longest >= kGroupKeys && launch_slots(longest) + beside <= kCus) {
-            int64_t c = base;
-            while (c < longest && launch_slots(c) + beside > kCus) c += std::max<int64_t>(kTileKeys, c / 8);
-            if (rounded(c) > rounded(base) && cost(rounded(c), true) < cost(rounded(base), false))
-                emitted = emit_tiles(rounded(c)) && takes_groups();  // padding of the order may still be in the way
-        }
-        if (!emitted) ok = emit_tiles(rounded(base));
+    int64_t total = 0, longest = 0, work = 0;
+    // workgroups of a unit's piece that have rows
+    auto filled = [&](const Unit& u) -> int64_t {
+        return P.num_kv_heads * (u.nrows == kTileRows ? G : ceil_div((int64_t)u.nrows * G, kTileRows));
+    };
+    for (const Unit& u : tile_units) {
+        const int64_t n = (int64_t)u.k_end - u.k_begin;
+        total += n;
+        longest = std::max(longest, n);
+        work += n * filled(u);
     }
+    auto split_at = [&](int32_t chunk) {
+        Split s;
+        for (const Unit& u : tile_units) {
+            int64_t nch, cs;
+            cut(u, chunk, kTileKeys, false, nch, cs);
+            s.piece = std::max(s.piece, cs);
+            s.rows += partial_slots(u, chunk, kTileKeys, false);
+            s.workgroups += nch * filled(u);
+            s.slots += nch * P.num_qo_heads;
+        }
+        return s;
+    };
+    const bool narrow = P.head_dim == 64;
+    auto merge_cost = [&](const Split& s) -> int64_t { return s.rows > 0 ? 400 + s.rows / (narrow ? 70 : 55) : 0; };
+    auto plain_cost = [&](const Split& s) {
+        const int64_t share = ceil_div(s.workgroups, kCus) * work / std::max<int64_t>(1, s.workgroups);
+        return std::max(share, s.piece + s.piece / 2) + merge_cost(s);
+    };
+    const int64_t beside = (P.flags & MSTAR_FLAG_SERIAL) ? 0 : std::min<int64_t>(kCus, few_items);
+    auto group_cost = [&](const Split& s) {
+        const int64_t held = std::max<int64_t>(0, beside + s.slots - kCus);
+        return s.piece + merge_cost(s) + held * (400 + few_keys / 200) / kCus;
+    };
+    auto rounded = [](int64_t c) {
+        return (int32_t)std::min<int64_t>(ceil_div(c, kTileKeys) * kTileKeys, INT32_MAX / 2);
+    };
+    auto longer = [](int64_t c) { return c + std::max<int64_t>(kTileKeys, c / 8); };
+    const bool force = (P.flags & MSTAR_FLAG_FORCE_SPLIT) != 0;
+    int32_t chunk = force ? kTileKeys * 2 : 0;
+    if (!force && !(P.flags & MSTAR_FLAG_NO_SPLIT) && longest > 0 && (int64_t)tile_units.size() * P.num_qo_heads < 512) {
+        int64_t c = std::max<int64_t>(1024, ceil_div(total, 1024));
+        chunk = rounded(c);
+        // A few long units whose partials pass the static scratch take pieces
+        // whose partials fit it, if some do that give every CU a workgroup at most.
+        const int64_t few_least = few_chunk == 0 ? few_slots(0) : std::min(few_slots(few_chunk), few_slots(few_coarse));
+        auto fits = [&](const Split& s) { return in_scratch(slot0 + s.rows + few_least); };
+        if (!fits(split_at(chunk)) && split_at(rounded(longest)).workgroups <= kCus) {
+            while (c < longest && split_at(rounded(c)).workgroups > kCus && !fits(split_at(rounded(c)))) c = longer(c);
+            if (fits(split_at(rounded(c)))) chunk = rounded(c);
+        }
+        int64_t least = plain_cost(split_at(chunk)) * (narrow ? 17 : 18) / 20;
+        for (c = chunk; c < longest;) {
+            c = longer(c);
+            const int64_t k = plain_cost(split_at(rounded(c)));
+            if (k < least) {
+                least = k;
+                chunk = rounded(c);
+            }
+        }
+    }
+    bool ok = true, emitted = false;
+    if (!force && longest >= kGroupKeys && split_at(0).slots <= kCus) {
+        int64_t c = chunk == 0 ? 0 : std::max<int64_t>(1024, ceil_div(total, 1024));
+        while (c > 0 && c < longest && split_at(rounded(c)).slots > kCus) c = longer(c);
+        const int32_t grouped = rounded(c);
+        if (group_cost(split_at(grouped)) < plain_cost(split_at(chunk))) {
+            ok = emit_tiles(grouped);
+            // the pieces and the order as they came out: equal parts, padding
+            plan.key_groups = plan.tile_order.size() / 2 <= (size_t)kCus && longest_of(plan.tiles) >= kGroupKeys;
+            emitted = plan.key_groups || grouped == chunk;
+        }
+    }
+    if (!emitted) ok = emit_tiles(chunk);
     if (!ok || !launch_order(plan.cascade, false, nullptr, plan.casc_order)) {
         err = "too many tile workgroups";
         return MSTAR_ERR_INVALID_ARG;
     }
-    plan.key_groups = takes_groups();
     plan.tile_span = longest_of(plan.tiles);
     plan.casc_span = longest_of(plan.cascade);
 
     // ---- 9. the few-row items -------------------------------------------------------
     if (few_chunk != 0 && !(P.flags & MSTAR_FLAG_FORCE_SPLIT)) {
-        auto in_scratch = [&](int32_t chunk) {
-            int64_t slots = slot;
-            for (const Unit& u : few_units) slots += partial_slots(u, chunk, kSubKeys, true);
-            return slots * (P.head_dim + 1) * 4 <= MSTAR_NOALLOC_SCRATCH_BYTES - 512;
-        };
-        if (!in_scratch(few_chunk) && in_scratch(few_coarse)) few_chunk = few_coarse;
+        if (!in_scratch(slot + few_slots(few_chunk)) && in_scratch(slot + few_slots(few_coarse))) few_chunk = few_coarse;
     }
     for (const Unit& u : few_units) emit(u, few_chunk, kSubKeys, plan.few, true);
     plan.partial_slots = slot;

@@ -60,3 +60,25 @@ def test_pool_past_2_gb():
 
     sb, q, kp, vp, rows = W.extract_requests(b, t, range(b.num_seqs))
     compare(b, out, lse, *oracle_attention(sb, q, kp, vp), "key groups, pool past 2 GB")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_beside_few_row_items(d):
+    """Key groups on the caller's stream, a little few-row work on the side stream."""
+    b = W.custom("groups_few", 4, 2, d, [900, 1, 1], [900, 300, 77], [[(0, n, W.SEG_CAUSAL, 0)] for n in (900, 300, 77)],
+                 [0, 0, 0], seed=d)
+    t = W.make_tensors_torch(b, DEV, poison_unused=True)
+    for flag in (0, attn.FLAG_SERIAL):
+        out, lse = run_gpu(b, t, flag, out_fill=float("nan"))
+        compare(b, out, lse, *oracle_of(b, t), f"key groups beside few rows d{d} flags {flag}")
+
+
+def test_long_pieces_without_groups():
+    """Partials of 1024-key pieces would pass the static scratch: longer ones."""
+    b = W.custom("long_pieces", 28, 4, 128, [640], [8000], [[(0, 8000, W.SEG_CAUSAL, 0)]], [0], seed=5)
+    pl = plan_for(b, attn.FLAG_HOST_ONLY)
+    it = pl.items(0)
+    assert (it[:, 5] - it[:, 4]).max() > 1024 and (it[:, 6] >= 0).all() and len(pl.tile_order()) > 256
+    pl.destroy()
+    t = W.make_tensors_torch(b, DEV)
+    compare(b, *run_gpu(b, t, out_fill=float("nan")), *oracle_of(b, t), "long pieces")

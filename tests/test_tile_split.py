@@ -1,6 +1,6 @@
-"""How multi-row items are cut into key pieces (CPU only).  Pieces longer than
-the ordinary ones are for launches whose workgroups share their keys among
-groups of waves: at most 256 launch slots, those without rows and few-row items beside them included."""
+"""How multi-row items are cut into key pieces (CPU only): longer pieces than the
+ordinary 1024 keys or more are cheaper by the planner's own measure, worked
+out here from the plan's items, or keep partials within the static scratch."""
 import itertools
 
 import pytest
@@ -9,49 +9,102 @@ import workloads as W
 from paper_2606_12688_amd import attn
 from tests.helpers import plan_for
 
-HEADS = [(28, 4, 128), (8, 2, 128), (16, 8, 64), (16, 16, 64)]
+CUS, SCRATCH = 256, 32 << 20
 
 
-def _pieces(reqs, hq, hkv, d, flags=0):
+def cdiv(a, b):
+    return -(-a // b)
+
+
+def _cost(items, hq, hkv, d, few=(0, 0)):
+    """(without key groups, with them) of tile items (keys, rows, partial): keys
+    walked by a CU's waves together."""
+    G = hq // hkv
+    wgs = [hkv * (G if r == 128 else cdiv(r * G, 128)) for _, r, _ in items]
+    work = sum(n * w for (n, _, _), w in zip(items, wgs))
+    rows = sum(r * hq for _, r, partial in items if partial)
+    merge = 400 + rows // (70 if d == 64 else 55) if rows else 0
+    piece = max(n for n, _, _ in items)
+    held = max(0, min(CUS, few[0]) + len(items) * hq - CUS)
+    return (max(cdiv(sum(wgs), CUS) * work // sum(wgs), piece + piece // 2) + merge,
+            piece + merge + held * (400 + few[1] // 200) // CUS)
+
+
+def _batch(reqs, hq, hkv, d):
     q, kv, win = ([r[k] for r in reqs] for k in range(3))
-    b = W.custom("split", hq, hkv, d, q, kv, [[(0, n, W.SEG_CAUSAL, 0)] for n in kv], win)
+    return W.custom("split", hq, hkv, d, q, kv, [[(0, n, W.SEG_CAUSAL, 0)] for n in kv], win)
+
+
+def _plan(b, flags=0):
+    """Tile items (keys, rows, partial), launch slots, few-row items and their
+    keys, bytes of partials."""
     pl = plan_for(b, attn.FLAG_HOST_ONLY | flags)
-    whole = plan_for(b, attn.FLAG_HOST_ONLY | attn.FLAG_NO_SPLIT)
-    span = lambda p: p.items(0)[:, 5] - p.items(0)[:, 4]
-    longest, total, units = span(pl).max(), span(whole).sum(), len(whole.items(0))
-    slots, few = len(pl.tile_order()), len(pl.items(1))
-    ordinary = -(-max(1024, -(-int(total) // 1024)) // 64) * 64
+    t, f = pl.items(0).tolist(), pl.items(1)
+    got = [(w[5] - w[4], w[3], w[6] >= 0) for w in t], len(pl.tile_order()), (len(f), int((f[:, 5] - f[:, 4]).sum())), \
+        pl.workspace_bytes
     pl.destroy()
-    whole.destroy()
-    return int(longest), ordinary, slots, few, units
+    return got
+
+
+def _ordinary(units):
+    """The units in equal pieces of about 1024 keys."""
+    chunk = cdiv(max(1024, cdiv(sum(n for n, _, _ in units), 1024)), 64) * 64
+    out = []
+    for n, r, _ in units:
+        if n > chunk:
+            size = cdiv(cdiv(n, cdiv(n, chunk)), 64) * 64
+            out += [(min(size, n - at), r, True) for at in range(0, n, size)]
+        else:
+            out.append((n, r, False))
+    return out
+
+
+def _check(reqs, hq, hkv, d):
+    b = _batch(reqs, hq, hkv, d)
+    items, slots, few, _ = _plan(b)
+    units = _plan(b, attn.FLAG_NO_SPLIT)[0]
+    if len(units) * hq >= 512:
+        assert sorted(items) == sorted(units)
+        return
+    ordinary = _ordinary(units)
+    if sorted(items) == sorted(ordinary):
+        return
+    limit = _cost(ordinary, hq, hkv, d)[0]
+    plain, groups = _cost(items, hq, hkv, d, few)
+    bytes_ordinary = sum(r * hq for _, r, p in ordinary if p) * (d + 1) * 4
+    assert plain <= limit or (slots <= CUS and groups < limit) or bytes_ordinary > SCRATCH // 2, \
+        (reqs, plain, groups, limit, slots)
 
 
 @pytest.mark.parametrize("reqs,heads", [
     ([(20, 8000, 0)] * 15, (28, 4, 128)), ([(16, 16000, 0)] * 12, (28, 4, 128)), ([(20, 8000, 4000)] * 8, (28, 4, 128)),
-    ([(640, 8000, 0)], (28, 4, 128)), ([(640, 20000, 0)], (28, 4, 128)), ([(1100, 32000, 0)], (16, 8, 64))])
-def test_launches_without_key_groups_keep_the_ordinary_pieces(reqs, heads):
-    longest, ordinary, _, _, _ = _pieces(reqs, *heads)
-    assert longest <= ordinary
+    ([(128, 6000, 0)] * 3, (28, 4, 128)), ([(300, 12000, 0)], (16, 8, 64)),
+    ([(1829, 1829, 0)] + [(1, 4000, 0)] * 64, (16, 8, 64))])
+def test_longer_pieces_are_cheaper(reqs, heads):
+    _check(reqs, *heads)
 
 
-@pytest.mark.parametrize("hq,hkv,d", HEADS)
+@pytest.mark.parametrize("hq,hkv,d", [(28, 4, 128), (8, 2, 128), (16, 8, 64), (16, 16, 64)])
 @pytest.mark.parametrize("n", [1, 3])
-def test_longer_pieces_only_for_key_groups(hq, hkv, d, n):
+def test_longer_pieces_are_cheaper_over_lengths(hq, hkv, d, n):
     for q, kv, win in itertools.product((65, 128, 300, 640, 1100), (1500, 4000, 12000, 32000), (0, 2000)):
-        longest, ordinary, slots, few, units = _pieces([(q, max(q, kv), win)] * n, hq, hkv, d)
-        if longest > ordinary and units * hq < 512:
-            assert slots + few <= 256, (q, kv, win)
+        _check([(q, max(q, kv), win)] * n, hq, hkv, d)
+
+
+@pytest.mark.parametrize("reqs,heads", [
+    ([(640, 8000, 0)], (28, 4, 128)), ([(640, 20000, 0)], (28, 4, 128)), ([(1100, 32000, 0)], (16, 8, 64)),
+    ([(1327, 8881, 0), (162, 3774, 2000)], (16, 8, 128))])
+def test_long_units_are_cut_evenly_within_the_scratch(reqs, heads):
+    """Requests whose pieces of 1024 keys would write 40-190 MB of partials:
+    pieces that fit the scratch, several workgroups for each CU."""
+    items, slots, _, workspace = _plan(_batch(reqs, *heads))
+    assert workspace <= SCRATCH and slots > CUS
+    n = [k for k, _, _ in items]
+    assert max(n) < 9000 and max(n) * len(n) <= 1.4 * sum(n)
 
 
 def test_long_equal_pieces_for_key_groups():
     """256 rows over 32000 keys at 8/2 heads: 16 pieces of 2048 keys for each
     of two row tiles fill the 256 slots."""
-    longest, ordinary, slots, _, _ = _pieces([(256, 32000, 0)], 8, 2, 128)
-    assert longest > ordinary and slots == 256
-
-
-@pytest.mark.parametrize("n,flags,same", [(0, 0, True), (8, 0, False), (8, attn.FLAG_SERIAL, True)])
-def test_few_row_work_beside_the_tiles_counts(n, flags, same):
-    """Two prompts of 1846 tokens fill the 256 slots whole; decode steps beside
-    them leave no CU to each."""
-    assert (_pieces([(1846, 1846, 0)] * 2 + [(1, 2000, 0)] * n, 8, 2, 128, flags)[0] == 1846) == same
+    items, slots, _, _ = _plan(_batch([(256, 32000, 0)], 8, 2, 128))
+    assert max(n for n, _, _ in items) == 2048 and slots == 256
