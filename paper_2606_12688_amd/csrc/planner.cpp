@@ -20,7 +20,8 @@
 //     128-row items over the decode-like members' (row, head) list and the
 //     members' own items start at the prefix end;
 //  4. split key ranges into chunks when there are too few items to fill the
-//     GPU (partials are merged by their log-sum-exps afterwards);
+//     GPU (partials are merged by their log-sum-exps afterwards); the tiles' split
+//     is chosen together with their launch order, since key groups depend on it;
 //  5. order every list longest first so that the hardware dispatcher, which
 //     starts workgroups in order as slots free up, ends with short items;
 //  6. lay out the multi-row workgroups (tiles, cascade items) so that the
@@ -728,7 +729,7 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
         return true;
     };
 
-    // ---- 7. pieces of the few-row units: enough to keep every CU streaming K/V ------
+    // ---- splits: the few-row units, in enough pieces to keep every CU streaming K/V ---
     int32_t few_chunk = 0, few_coarse = 0;  // keys per piece; the same where only these partials fit the static scratch
     if (P.flags & MSTAR_FLAG_FORCE_SPLIT) {
         few_chunk = kSubKeys * 2;
@@ -773,7 +774,7 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
         return n;
     };
 
-    // ---- 8. the multi-row items: their pieces, key groups, launch order ------------
+    // ---- splits: the multi-row items, their key groups and launch order ---------------
     // Items in pieces of `chunk` keys (0: whole), longest first, and their order;
     // may be called again with another chunk.
     std::vector<int64_t> tile_pairs;  // visible pairs of each tile item, for the launch order
@@ -898,7 +899,7 @@ int build_host_plan(const mstar_attn_params* params, const mstar_seq_desc* seqs,
     plan.tile_span = longest_of(plan.tiles);
     plan.casc_span = longest_of(plan.cascade);
 
-    // ---- 9. the few-row items -------------------------------------------------------
+    // ---- the few-row items -------------------------------------------------------------
     if (few_chunk != 0 && !(P.flags & MSTAR_FLAG_FORCE_SPLIT)) {
         if (!in_scratch(slot + few_slots(few_chunk)) && in_scratch(slot + few_slots(few_coarse))) few_chunk = few_coarse;
     }
